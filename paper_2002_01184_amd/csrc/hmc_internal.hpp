@@ -38,7 +38,6 @@ struct Workspace {
     double* h0;    // [C] initial energy
     float* part_g;     // [nsplit, C, D] split-N gradient partials (LOGREG plain)
     double* part_lp;   // [nsplit, C]
-    int32_t* lr_cnt;   // [ceil(C / 64)] finished splits per chain tile of the FP32 logistic step (0 between launches)
     void* xt;          // [DP, NP] BF16 zero-padded transposed copy of X (BF16 gradients only)
     void* xp;          // [NP, DP] BF16 zero-padded copy of X
     void* yp;          // [NP] labels, zeros past N
@@ -112,8 +111,13 @@ inline void timer_end(const PlainArgs& a, hipStream_t s, const char* name) {
         ++t->n;
     }
 }
-int64_t logreg_nsplit_t(const PlainArgs& a);
 int lb_grad_nsplit_t(const PlainArgs& a);
+// ---- FP32 logistic gradient (k_logreg_f32.hip) -------------------------------
+int64_t lr32_rows(int64_t N, int64_t nsplit);   // rows of each split
+int lr32_nsplit(const PlainArgs& a);
+// gradient (and logp) partials of every split at x (drifted by p when drift)
+hipError_t launch_lr32_grad(const PlainArgs& a, const float* x, const float* p, int drift, int want_logp, int nsplit,
+                            int64_t rows, hipStream_t s);
 hipError_t launch_set_ctrl(const Ctrl& c, Ctrl* dst, hipStream_t s);
 hipError_t launch_bootstrap(const PlainArgs& a, const void* x_src, hipStream_t s);
 hipError_t launch_plain_transition(const PlainArgs& a, bool copy_proposal, hipStream_t s);

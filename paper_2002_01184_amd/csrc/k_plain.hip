@@ -837,21 +837,33 @@ __global__ __launch_bounds__(64 * DS_NW) void k_dense_step(PlainArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Logistic regression, split over rows.  Workgroup (chain tile of 16, split s)
-// handles rows [s*rows, (s+1)*rows).  Per 16-row tile:
-//   S = X_tile theta^T   (M = rows, N = chains, K = dims)      16x16x4 MFMA
-//   R = y - sigmoid(S)   (rows beyond N give 0)
-//   G += X_tile^T R      (M = dims, N = chains, K = 4 rows)    K-step v takes the
-//       rows {4k + v}, so the B operand is the S accumulator's own VGPR v.
-// Wave partials are summed in LDS in wave order, then written to part_g[s].
+// Logistic regression: the gradient partials of each row split (k_logreg_f32.hip,
+// k_logreg_bf16.hip) summed here.
 // ---------------------------------------------------------------------------
-template <typename XT>
-__device__ __forceinline__ float ld_x(const XT* X, int64_t i);
-template <>
-__device__ __forceinline__ float ld_x<float>(const float* X, int64_t i) { return X[i]; }
-template <>
-__device__ __forceinline__ float ld_x<uint16_t>(const uint16_t* X, int64_t i) { return bf16_to_f32(X[i]); }
-
+// ---------------------------------------------------------------------------
+// Logistic regression, D <= 32, FP32 gradients: the gradient and log-likelihood
+// partials at a given state (bootstrap, set_state) on v_mfma_f32_16x16x4f32.
+// Runs of these shapes go through the fused and the persistent NUTS kernels,
+// which form their own gradients and only start from this one: it keeps the
+// arithmetic, so that a seed's chains stay the same bit for bit, where the
+// split kernel (k_logreg_f32.hip) rounds differently.  Every leapfrog step of
+// the plain form runs there.
+// A workgroup (4 waves) owns 64 chains and one split of the rows; wave w runs
+// both contractions for chains c0 + 16 w + i16 over the split's rows, 16 rows
+// at a time:
+//   S = X_sub theta^T  (M = 16 rows, N = 16 chains, K = 4 dims): k-step (b, v)
+//                      takes dims 16 b + 4 q + v at lane group q, so one
+//                      16-byte LDS read gives the A operands of 4 k-steps and
+//                      lane (i16, q) holds theta of dims 16 b + 4 q .. + 3 as B
+//   R = y - sigmoid(S) (0 for rows outside the split)
+//   G += X_sub^T R     (M = 16 dims, N = 16 chains, K = 4 rows): k-step v takes
+//                      rows 4 q + v, the S accumulator's own VGPR v
+// X (FP32, upcast when stored BF16) is double-buffered in LDS through
+// registers (row stride 16 KT + 4 floats: both operand reads hit distinct
+// banks).  The partials are summed in split order by k_logreg_finish (summing
+// them in the last workgroup of a tile to finish had taken 88 us for the launch
+// at 10000 x 25, 1024 chains, most of it that workgroup's).
+// ---------------------------------------------------------------------------
 __device__ __forceinline__ float sigmoidf_(float s) {
     // 1 / (1 + e^-s) evaluated without overflow on either side
     const float e = expf(-fabsf(s));
@@ -863,35 +875,12 @@ __device__ __forceinline__ float softplusf_(float s) {
     return fmaxf(s, 0.f) + log1pf(expf(-fabsf(s)));
 }
 
-// ---------------------------------------------------------------------------
-// Logistic regression, FP32 operands: one launch per leapfrog step.
-// A workgroup (4 waves) owns 64 chains and one split of the rows; wave w runs
-// both contractions for chains c0 + 16 w + i16 over the split's rows on
-// v_mfma_f32_16x16x4f32, 16 rows at a time:
-//   S = X_sub theta^T  (M = 16 rows, N = 16 chains, K = 4 dims): k-step (b, v)
-//                      takes dims 16 b + 4 q + v at lane group q, so one
-//                      16-byte LDS read gives the A operands of 4 k-steps and
-//                      lane (i16, q) holds theta of dims 16 b + 4 q .. + 3 as B
-//   R = y - sigmoid(S) (0 for rows outside the split)
-//   G += X_sub^T R     (M = 16 dims, N = 16 chains, K = 4 rows): k-step v takes
-//                      rows 4 q + v, the S accumulator's own VGPR v
-// theta (drifted) stays in VGPRs, G in KT accumulators; 16-row stages of X
-// (FP32, upcast when stored BF16) are double-buffered in LDS through
-// registers and shared by the 4 waves (row stride 16 KT + 4 floats: both
-// operand reads hit distinct banks).  Each workgroup writes its partial G and
-// logp to part_g / part_lp; the last one of a chain tile to finish (an atomic
-// count per tile, reset by that workgroup) sums the partials in split order,
-// adds the prior gradient, kicks and writes x, p, g and the data part of logp
-// -- the partial-sum and finish passes in one launch, in a fixed order.
-// ---------------------------------------------------------------------------
 constexpr int LR32_CT = 64;      // chains per workgroup
 constexpr int LR32_RS = 16;      // rows per sub-tile (one M tile of S)
 
-// rows per LDS stage: 16 for 128 dims and more, else 128 / KT (8 stage elements
-// per thread in every case below 256 dims), so that narrow problems do not wait
-// on one global load latency per 16 rows
+// rows per LDS stage: 8 stage elements per thread
 template <int KT>
-constexpr int lr32_rs() { return KT >= 8 ? 16 : 128 / KT; }
+constexpr int lr32_rs() { return 128 / KT; }
 
 template <typename XT>
 struct Lr32Stage;
@@ -993,15 +982,12 @@ __device__ __forceinline__ uint32_t lr32_label(const uint8_t* y, int64_t r_begin
 }
 
 template <typename XT, int KT, bool VEC>
-__global__ __launch_bounds__(256) void k_lr32_step(PlainArgs a, float* __restrict__ xio, float* __restrict__ pio,
-                                                   float* __restrict__ gout, int drift, int kick, double kick_scale,
-                                                   int want_logp, int nsplit, int64_t rows_per_split) {
+__global__ __launch_bounds__(256) void k_lr32_boot(PlainArgs a, const float* __restrict__ x, int64_t rows_per_split) {
     constexpr int XS = 16 * KT + 4;                       // LDS row stride (floats)
     constexpr int RS = lr32_rs<KT>();                    // rows per stage
     constexpr int STAGE = RS * XS;
     extern __shared__ float lds[];                        // [2][RS][XS] X stages, then [2][RS] labels
     float* ys = lds + 2 * STAGE;
-    __shared__ int s_last;
     const int64_t D = a.tg.D, N = a.tg.N, C = a.C;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int i16 = lane & 15, q = lane >> 4;
@@ -1010,39 +996,18 @@ __global__ __launch_bounds__(256) void k_lr32_step(PlainArgs a, float* __restric
     const bool cv = c < C;
     const XT* X = (const XT*)a.tg.X;
     const uint8_t* y = a.tg.y;
-    const double* sc = a.ws.scale;
-    const double eps = cv ? a.ws.eps[c] : 0.0;
 
-    // theta (drifted) as B operands: th[b][v] = theta[c][16 b + 4 q + v], loaded
-    // four 16-dim blocks at a time with every load of a group issued before its
-    // arithmetic (the drift is the same fmaf as the finish below, which stores
-    // the drifted x)
+    // theta as B operands: th[b][v] = theta[c][16 b + 4 q + v]
     float th[KT][4];
     const int64_t cr = (cv ? c : 0) * D;
-    constexpr int PB = KT < 4 ? KT : 4;
 #pragma unroll
-    for (int b0 = 0; b0 < KT; b0 += PB) {
-        float pm[PB][4];
+    for (int b = 0; b < KT; ++b)
 #pragma unroll
-        for (int bb = 0; bb < PB; ++bb)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int64_t d = 16 * (b0 + bb) + 4 * q + v;
-                const int64_t dd = d < D ? d : 0;
-                th[b0 + bb][v] = xio[cr + dd];
-                pm[bb][v] = drift ? pio[cr + dd] : 0.f;
-            }
-#pragma unroll
-        for (int bb = 0; bb < PB; ++bb)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int64_t d = 16 * (b0 + bb) + 4 * q + v;
-                const bool ok = cv && d < D;
-                float t = th[b0 + bb][v];
-                if (drift) t = fmaf(sc ? (float)(eps * sc[ok ? d : 0]) : (float)eps, pm[bb][v], t);
-                th[b0 + bb][v] = ok ? t : 0.f;
-            }
-    }
+        for (int v = 0; v < 4; ++v) {
+            const int64_t d = 16 * b + 4 * q + v;
+            const float t = x[cr + (d < D ? d : 0)];
+            th[b][v] = cv && d < D ? t : 0.f;
+        }
 
     const int64_t r_begin = (int64_t)split * rows_per_split;
     const int64_t r_end = r_begin + rows_per_split < N ? r_begin + rows_per_split : N;
@@ -1098,7 +1063,7 @@ __global__ __launch_bounds__(256) void k_lr32_step(PlainArgs a, float* __restric
                 const bool ok = r0 + 4 * q + v < r_end;
                 const float yv = ys[buf * RS + LR32_RS * h + 4 * q + v];
                 rr[v] = ok ? yv - sigmoidf_(sv) : 0.f;
-                if (want_logp && ok) lp -= (double)softplusf_(yv > 0.5f ? -sv : sv);
+                if (ok) lp -= (double)softplusf_(yv > 0.5f ? -sv : sv);
             }
             // G += X_sub^T R
 #pragma unroll
@@ -1129,112 +1094,55 @@ __global__ __launch_bounds__(256) void k_lr32_step(PlainArgs a, float* __restric
     }
     lp += __shfl_xor(lp, 16, 64);
     lp += __shfl_xor(lp, 32, 64);
-    if (want_logp && cv && q == 0) a.ws.part_lp[(int64_t)split * C + c] = lp;
-    // release this workgroup's partials (agent scope: the other splits may run on other XCDs),
-    // then count it; the last one to count acquires them all
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __syncthreads();
-    if (threadIdx.x == 0) s_last = atomicAdd(&a.ws.lr_cnt[tile], 1) == nsplit - 1;
-    __syncthreads();
-    if (!s_last) return;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (cv && q == 0) a.ws.part_lp[(int64_t)split * C + c] = lp;
+}
 
-    // last workgroup of the tile: drift (the same fmaf), split sum in split order,
-    // prior gradient, kick -- four elements per thread at a time, every load of
-    // the four (state, step size, split partials) issued before the arithmetic
-    const int64_t c0 = (int64_t)tile * LR32_CT;
-    const int64_t nc = C - c0 < LR32_CT ? C - c0 : LR32_CT;
-    const int64_t ne = nc * D;
-    constexpr int U = 4;
-    for (int64_t base = threadIdx.x; base < ne; base += 256 * U) {
-        float xv[U], pv[U], gs[U];
-        double ec[U], sd[U], bt[U];
+// Sum of p[s * stride], s = 0 .. n - 1, in that order, with up to 32 loads in
+// flight (a load per add waits for each: 64 splits would cost 64 L2 latencies).
+template <typename T>
+__device__ __forceinline__ T split_sum(const T* __restrict__ p, int64_t stride, int n) {
+    T sum = (T)0;
+    int s0 = 0;
+    for (; s0 + 32 <= n; s0 += 32) {
+        T v[32];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t idx = base + 256 * u < ne ? base + 256 * u : ne - 1;    // clamped: loads stay in range
-            const int64_t i = c0 * D + idx;
-            const int64_t cc = i / D, d = i - cc * D;
-            ec[u] = a.ws.eps[cc];
-            sd[u] = sc ? sc[d] : 1.0;
-            bt[u] = a.ws.beta ? a.ws.beta[cc] : 1.0;
-            xv[u] = xio[i];
-            pv[u] = (drift || kick) ? pio[i] : 0.f;
-            gs[u] = 0.f;
-        }
-        for (int s0 = 0; s0 < nsplit; s0 += 8) {
-            float v[U][8];
+        for (int k = 0; k < 32; ++k) v[k] = p[(int64_t)(s0 + k) * stride];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int64_t idx = base + 256 * u < ne ? base + 256 * u : ne - 1;
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const int sk = s0 + k < nsplit ? s0 + k : nsplit - 1;
-                    v[u][k] = a.ws.part_g[(int64_t)sk * CD + c0 * D + idx];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int k = 0; k < 8; ++k)
-                    if (s0 + k < nsplit) gs[u] += v[u][k];
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (base + 256 * u >= ne) continue;
-            const int64_t i = c0 * D + base + 256 * u;
-            float x = xv[u];
-            if (drift) {
-                x = fmaf(sc ? (float)(ec[u] * sd[u]) : (float)ec[u], pv[u], x);
-                xio[i] = x;
-            }
-            const float gv = gs[u] - x * (float)a.tg.inv_var;
-            if (kick) pio[i] = fmaf((float)(kick_scale * ec[u] * bt[u] * sd[u]), gv, pv[u]);
-            if (gout) gout[i] = gv;
-        }
+        for (int k = 0; k < 32; ++k) sum += v[k];
     }
-    if (want_logp && threadIdx.x < nc) {
-        const int64_t cc = c0 + threadIdx.x;
-        // eight loads in flight, then the sums in split order
-        double l = 0.0;
-        for (int s0 = 0; s0 < nsplit; s0 += 8) {
-            double v[8];
+    for (; s0 < n; s0 += 8) {
+        T v[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = a.ws.part_lp[(int64_t)(s0 + k < nsplit ? s0 + k : nsplit - 1) * C + cc];
+        for (int k = 0; k < 8; ++k) v[k] = p[(int64_t)(s0 + k < n ? s0 + k : n - 1) * stride];
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (s0 + k < nsplit) l += v[k];
-        }
-        a.ws.lpq[cc] = l;
+        for (int k = 0; k < 8; ++k)
+            if (s0 + k < n) sum += v[k];
     }
-    if (threadIdx.x == 0) a.ws.lr_cnt[tile] = 0;
+    return sum;
 }
 
 // drift (same fmaf as the partial kernel), sum the split partials in split
-// order, add the prior gradient, kick.
+// order, add the prior gradient, kick.  Bound by latency and the partials' bytes.
 __device__ __forceinline__ void finish_body(const PlainArgs& a, float* __restrict__ xd, float* __restrict__ pd,
                                             float* __restrict__ gd, int nsplit, int drift, int kick,
                                             double kick_scale, int want_logp, int64_t blk, int64_t nblk) {
     const int64_t D = a.tg.D, C = a.C;
     const int64_t n = C * D;
     for (int64_t i = blk * blockDim.x + threadIdx.x; i < n; i += nblk * blockDim.x) {
-        const int64_t c = i / D;
-        const double sd = a.ws.scale ? a.ws.scale[i - c * D] : 1.0;
+        const int64_t c = n <= 0x7fffffff ? (int64_t)((uint32_t)i / (uint32_t)D) : i / D;
         float x = xd[i];
         const float p = (drift || kick) ? pd[i] : 0.f;
+        const double eps = a.ws.eps[c], bt = a.ws.beta ? a.ws.beta[c] : 1.0;
+        const double sd = a.ws.scale ? a.ws.scale[i - c * D] : 1.0;
+        const float gsum = split_sum(a.ws.part_g + i, n, nsplit);
         if (drift) {
-            x = fmaf(a.ws.scale ? (float)(a.ws.eps[c] * sd) : (float)a.ws.eps[c], p, x);
+            x = fmaf(a.ws.scale ? (float)(eps * sd) : (float)eps, p, x);
             xd[i] = x;
         }
-        float gsum = 0.f;
-        for (int s = 0; s < nsplit; ++s) gsum += a.ws.part_g[(int64_t)s * n + i];
         const float gv = gsum - x * (float)a.tg.inv_var;
-        if (kick) pd[i] = fmaf((float)(kick_scale * a.ws.eps[c] * (a.ws.beta ? a.ws.beta[c] : 1.0) * sd), gv, p);
+        if (kick) pd[i] = fmaf((float)(kick_scale * eps * bt * sd), gv, p);
         if (gd) gd[i] = gv;
-        if (want_logp && i - c * D == 0) {
-            double l = 0.0;
-            for (int s = 0; s < nsplit; ++s) l += a.ws.part_lp[(int64_t)s * C + c];
-            a.ws.lpq[c] = l;
-        }
+        if (want_logp && i - c * D == 0) a.ws.lpq[c] = split_sum(a.ws.part_lp + c, C, nsplit);
     }
 }
 
@@ -1346,72 +1254,57 @@ static hipError_t launch_dense(const PlainArgs& a, const float* xs, float* xd, f
 // largest split count the workspace is sized for (the autotuner tries up to 2x the default)
 int64_t logreg_nsplit_cap(int64_t N, int64_t C) {
     int64_t cap = 2 * logreg_nsplit(N, C);
-    const int64_t maxs = (N + 4 * LR32_RS - 1) / (4 * LR32_RS);
+    const int64_t maxs = (N + 63) / 64;
     if (cap > maxs) cap = maxs;
     if (cap > 64) cap = 64;
     return cap < 1 ? 1 : cap;
 }
 
-int64_t logreg_nsplit_t(const PlainArgs& a) {
+template <typename XT, int KT>
+static void launch_lr32_boot_kt(const PlainArgs& a, dim3 grid, int64_t rows, bool vec, hipStream_t s) {
+    constexpr int RS = lr32_rs<KT>();
+    const size_t lds = (size_t)(2 * RS * (16 * KT + 4) + 2 * RS) * sizeof(float);
+    const float* x = (const float*)a.ws.x;
+    if (vec) hipLaunchKernelGGL((k_lr32_boot<XT, KT, true>), grid, dim3(256), lds, s, a, x, rows);
+    else hipLaunchKernelGGL((k_lr32_boot<XT, KT, false>), grid, dim3(256), lds, s, a, x, rows);
+}
+
+// The partials of the bootstrap gradient for D <= 32; the number of splits.
+static int launch_lr32_boot(const PlainArgs& a, hipStream_t s) {
+    int64_t want = logreg_nsplit(a.tg.N, a.C);
     if (a.tune.lr_nsplit > 0) {
         const int64_t cap = logreg_nsplit_cap(a.tg.N, a.C);
-        return a.tune.lr_nsplit < cap ? a.tune.lr_nsplit : cap;
+        want = a.tune.lr_nsplit < cap ? a.tune.lr_nsplit : cap;
     }
-    return logreg_nsplit(a.tg.N, a.C);
-}
-
-template <int KT>
-static size_t lr32_lds() {
-    constexpr int RS = lr32_rs<KT>();
-    return (size_t)(2 * RS * (16 * KT + 4) + 2 * RS) * sizeof(float);
-}
-
-template <typename XT, int KT>
-static void launch_lr32_kt(const PlainArgs& a, dim3 grid, hipStream_t s, float* x, float* p, float* gd, int drift,
-                           int kick, double ks, int want_logp, int nsplit, int64_t rows, int vec) {
-    const size_t lds = lr32_lds<KT>();
-    if (vec) {
-        allow_lds(k_lr32_step<XT, KT, true>, lds);
-        hipLaunchKernelGGL((k_lr32_step<XT, KT, true>), grid, dim3(256), lds, s, a, x, p, gd, drift, kick, ks,
-                           want_logp, nsplit, rows);
+    int64_t rows = (a.tg.N + want - 1) / want;
+    rows = (rows + LR32_RS - 1) / LR32_RS * LR32_RS;
+    const int nsplit = (int)((a.tg.N + rows - 1) / rows);
+    const dim3 grid((unsigned)((a.C + LR32_CT - 1) / LR32_CT), (unsigned)nsplit);
+    const bool al = ((uintptr_t)a.tg.X & 15) == 0;
+    if (a.tg.x_bf16) {
+        if (a.tg.D <= 16) launch_lr32_boot_kt<uint16_t, 1>(a, grid, rows, a.tg.D % 8 == 0 && al, s);
+        else launch_lr32_boot_kt<uint16_t, 2>(a, grid, rows, a.tg.D % 8 == 0 && al, s);
     } else {
-        allow_lds(k_lr32_step<XT, KT, false>, lds);
-        hipLaunchKernelGGL((k_lr32_step<XT, KT, false>), grid, dim3(256), lds, s, a, x, p, gd, drift, kick, ks,
-                           want_logp, nsplit, rows);
+        if (a.tg.D <= 16) launch_lr32_boot_kt<float, 1>(a, grid, rows, a.tg.D % 4 == 0 && al, s);
+        else launch_lr32_boot_kt<float, 2>(a, grid, rows, a.tg.D % 4 == 0 && al, s);
     }
-}
-
-template <typename XT>
-static void launch_lr32(const PlainArgs& a, dim3 grid, hipStream_t s, float* x, float* p, float* gd, int drift,
-                        int kick, double ks, int want_logp, int nsplit, int64_t rows, int vec) {
-    const int kt = (int)((a.tg.D + 15) / 16);
-    if (kt <= 1) launch_lr32_kt<XT, 1>(a, grid, s, x, p, gd, drift, kick, ks, want_logp, nsplit, rows, vec);
-    else if (kt <= 2) launch_lr32_kt<XT, 2>(a, grid, s, x, p, gd, drift, kick, ks, want_logp, nsplit, rows, vec);
-    else if (kt <= 4) launch_lr32_kt<XT, 4>(a, grid, s, x, p, gd, drift, kick, ks, want_logp, nsplit, rows, vec);
-    else if (kt <= 8) launch_lr32_kt<XT, 8>(a, grid, s, x, p, gd, drift, kick, ks, want_logp, nsplit, rows, vec);
-    else if (kt <= 16) launch_lr32_kt<XT, 16>(a, grid, s, x, p, gd, drift, kick, ks, want_logp, nsplit, rows, vec);
-    else launch_lr32_kt<XT, 32>(a, grid, s, x, p, gd, drift, kick, ks, want_logp, nsplit, rows, vec);
+    return nsplit;
 }
 
 // One FP32 gradient evaluation of logistic regression at x (drifted in place
 // first when drift), kicking p when kick, the gradient into gd if not null and
-// the data part of logp into lpq when want_logp.
+// the data part of logp into lpq when want_logp: the split partials, then their
+// sum.
 static hipError_t launch_logreg(const PlainArgs& a, float* x, float* p, float* gd, int drift, int kick, double ks,
                                 int want_logp, hipStream_t s) {
-    int64_t nsplit = logreg_nsplit_t(a);
-    int64_t rows = (a.tg.N + nsplit - 1) / nsplit;
-    rows = (rows + LR32_RS - 1) / LR32_RS * LR32_RS;
-    nsplit = (a.tg.N + rows - 1) / rows;
-    const dim3 grid((unsigned)((a.C + LR32_CT - 1) / LR32_CT), (unsigned)nsplit);
-    const bool x_aligned = ((uintptr_t)a.tg.X & 15) == 0;
+    const int64_t rows = lr32_rows(a.tg.N, lr32_nsplit(a));
+    const int nsplit = (int)((a.tg.N + rows - 1) / rows);
     timer_begin(a, s);
-    if (a.tg.x_bf16)
-        launch_lr32<uint16_t>(a, grid, s, x, p, gd, drift, kick, ks, want_logp, (int)nsplit, rows,
-                              a.tg.D % 8 == 0 && x_aligned);
-    else
-        launch_lr32<float>(a, grid, s, x, p, gd, drift, kick, ks, want_logp, (int)nsplit, rows,
-                           a.tg.D % 4 == 0 && x_aligned);
+    const hipError_t e = launch_lr32_grad(a, x, p, drift, want_logp, nsplit, rows, s);
     timer_end(a, s, "k_lr32_step");
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_logreg_finish, elem_grid(a.C * a.tg.D), dim3(256), 0, s, a, x, p, gd, nsplit, drift, kick,
+                       ks, want_logp);
     return hipGetLastError();
 }
 
@@ -1463,10 +1356,6 @@ __global__ __launch_bounds__(256) void k_moments(const T* __restrict__ ring, int
         m2[e] = ss[0];
         m2[n_el + e] = ss[1];
     }
-}
-
-__global__ void k_zero_i32(int32_t* p, int64_t n) {
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
 }
 
 __global__ void k_fill_f64(double* p, int64_t n) {
@@ -1541,8 +1430,13 @@ hipError_t launch_bootstrap(const PlainArgs& a_in, const void* x_src, hipStream_
                                (float*)nullptr, (float*)a.ws.g, lb_grad_nsplit_t(a), 0, 0, 0.0, 0);
             (void)launch_lr16_logp(a, (const float*)a.ws.x, s);
         } else {
-            hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(256), 0, s, a.ws.lr_cnt, (a.C + LR32_CT - 1) / LR32_CT);
-            (void)launch_logreg(a, (float*)a.ws.x, nullptr, (float*)a.ws.g, 0, 0, 0.0, 1, s);
+            if (a.tg.D <= 32) {
+                const int nsplit = launch_lr32_boot(a, s);
+                hipLaunchKernelGGL(k_logreg_finish, elem_grid(a.C * a.tg.D), dim3(256), 0, s, a, (float*)a.ws.x,
+                                   (float*)nullptr, (float*)a.ws.g, nsplit, 0, 0, 0.0, 1);
+            } else {
+                (void)launch_logreg(a, (float*)a.ws.x, nullptr, (float*)a.ws.g, 0, 0, 0.0, 1, s);
+            }
         }
         break;
     }
