@@ -112,6 +112,11 @@ inline void timer_end(const PlainArgs& a, hipStream_t s, const char* name) {
     }
 }
 int lb_grad_nsplit_t(const PlainArgs& a);
+// ---- dense Gaussian gradient (k_dense_grad.hip) -------------------------------
+// g = -P x into gd (or NULL); with p, the kick p += kick_scale eps beta g; with
+// xnext (another buffer than x), the drifted x + eps p
+hipError_t launch_dense_grad(const PlainArgs& a, const float* x, float* xnext, float* p, float* gd, double kick_scale,
+                             hipStream_t s);
 // ---- FP32 logistic gradient (k_logreg_f32.hip) -------------------------------
 int64_t lr32_rows(int64_t N, int64_t nsplit);   // rows of each split
 int lr32_nsplit(const PlainArgs& a);

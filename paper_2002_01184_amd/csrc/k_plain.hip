@@ -21,6 +21,7 @@
 // Gradient kernels:
 //   elementwise   N(0, I) and diagonal Gaussians: one thread per (chain, dim)
 //   dense         g = -P x on MFMA (v_mfma_f32_16x16x4f32), 16 chains per workgroup
+//                 (beyond D = 128, bootstrap and NUTS leaves: k_dense_grad.hip)
 //   logreg        s = X theta, r = y - sigmoid(s), g = X^T r - theta/s^2 on MFMA,
 //                 rows split across workgroups with partials reduced in a fixed order
 #include "hmc_internal.hpp"
@@ -41,8 +42,10 @@ __global__ void k_tick(Ctrl* c) {
 // Chain-group kernels: G lanes of a wavefront share one chain; each lane owns
 // the 4-dim Philox blocks b = lane, lane + G, ...
 // ---------------------------------------------------------------------------
+// drift_to (dense Gaussian beyond D = 128): the first drift x + eps p goes there
+// instead of the copy of x into xq.
 template <typename T, int G>
-__device__ __forceinline__ void begin_body(const PlainArgs& a, int64_t blk) {
+__device__ __forceinline__ void begin_body(const PlainArgs& a, int64_t blk, T* drift_to = nullptr) {
     const int64_t gid = blk * blockDim.x + threadIdx.x;
     const int lane = threadIdx.x % G;
     const int64_t c = gid / G;
@@ -66,10 +69,16 @@ __device__ __forceinline__ void begin_body(const PlainArgs& a, int64_t blk) {
                 const int64_t d = 4 * b + j;
                 if (d < D) {
                     const int64_t i = c * D + d;
-                    xq[i] = x[i];
                     k0 += 0.5 * (double)z[j] * (double)z[j];
                     const T hk = a.ws.scale ? (T)(0.5 * a.ws.eps[c] * bt * a.ws.scale[d]) : half_eps;
-                    pq[i] = z[j] + hk * g[i];
+                    const T p = z[j] + hk * g[i];
+                    pq[i] = p;
+                    if (drift_to) {
+                        const T e = a.ws.scale ? (T)(a.ws.eps[c] * a.ws.scale[d]) : (T)a.ws.eps[c];
+                        drift_to[i] = fma(e, p, x[i]);
+                    } else {
+                        xq[i] = x[i];
+                    }
                 }
             }
         }
@@ -80,6 +89,22 @@ __device__ __forceinline__ void begin_body(const PlainArgs& a, int64_t blk) {
 
 template <typename T, int G>
 __global__ __launch_bounds__(256) void k_begin(PlainArgs a) { begin_body<T, G>(a, blockIdx.x); }
+
+__global__ __launch_bounds__(256) void k_begin_drift(PlainArgs a, float* drift_to) {
+    begin_body<float, 64>(a, blockIdx.x, drift_to);
+}
+
+// x += eps p on the trajectory buffers (the NUTS leaves of the dense Gaussian)
+__global__ __launch_bounds__(256) void k_drift(PlainArgs a) {
+    const int64_t D = a.tg.D, n = a.C * D;
+    float* x = (float*)a.ws.xq;
+    const float* p = (const float*)a.ws.pq;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t c = i / D;
+        const double e = a.ws.eps[c];
+        x[i] = fmaf(a.ws.scale ? (float)(e * a.ws.scale[i - c * D]) : (float)e, p[i], x[i]);
+    }
+}
 
 // logp at (x, g) from the closed form that remains after the gradient kernel:
 // Gaussians 1/2 x.g; logistic regression -|x|^2/(2 s^2) + the data part in lpq.
@@ -522,79 +547,6 @@ __global__ __launch_bounds__(256) void k_elem_last(PlainArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Dense Gaussian: g = -P x with v_mfma_f32_16x16x4f32.
-// Operand layouts (16x16x4, wave64): A[i][k] at lane i + 16 k; B[k][j] at
-// lane j + 16 k; D[i][j] in VGPR v of lane j + 16 (i / 4) with v = i % 4.
-// Chains are the N dimension (16 per workgroup), rows of P the M dimension;
-// wave w owns M-tiles w, w + 4, ...  x^T is staged in LDS as xs[d][chain].
-// ---------------------------------------------------------------------------
-template <int MT>
-__global__ __launch_bounds__(256) void k_dense_leapfrog(PlainArgs a, const float* __restrict__ xsrc,
-                                                        float* __restrict__ xdst, float* __restrict__ pd,
-                                                        float* __restrict__ gd, int mode, double kick_scale) {
-    extern __shared__ float lds[];
-    const int64_t D = a.tg.D;
-    const int ntiles = (int)((D + 15) / 16);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int i16 = lane & 15, g4 = lane >> 4;
-    const int64_t c = (int64_t)blockIdx.x * 16 + i16;
-    const bool cvalid = c < a.C;
-    const float* P = (const float*)a.tg.prec;
-    const float eps = cvalid ? (float)a.ws.eps[c] : 0.f;
-    const float keps = cvalid ? (float)(kick_scale * a.ws.eps[c] * (a.ws.beta ? a.ws.beta[c] : 1.0)) : 0.f;
-    float* xs = lds;   // [16 * ntiles][17]
-
-    float xr[MT][4], pr[MT][4];
-#pragma unroll
-    for (int m = 0; m < MT; ++m) {
-        const int mt = w + 4 * m;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int64_t d = 16 * mt + 4 * g4 + v;
-            const bool ok = mt < ntiles && d < D && cvalid;
-            float xv = ok ? xsrc[c * D + d] : 0.f;
-            float pv = (ok && (mode & 3)) ? pd[c * D + d] : 0.f;
-            const float ed = (ok && a.ws.scale) ? (float)(a.ws.eps[c] * a.ws.scale[d]) : eps;
-            if (mode & 1) xv = fmaf(ed, pv, xv);
-            xr[m][v] = xv;
-            pr[m][v] = pv;
-            if (mt < ntiles) xs[(16 * mt + 4 * g4 + v) * 17 + i16] = xv;
-        }
-    }
-    __syncthreads();
-    const int KM = 4 * ntiles;
-#pragma unroll
-    for (int m = 0; m < MT; ++m) {
-        const int mt = w + 4 * m;
-        if (mt >= ntiles) break;
-        // k-step ks, lane group g4 takes dim g4 KM + ks, with KM = 4 ntiles; even
-        // and odd k-steps in two accumulators: the same MFMA sequence as the
-        // fused kernel, so both forms give bitwise the same gradient
-        floatx4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-        const int64_t row = 16 * mt + i16;
-        for (int ks = 0; ks < KM; ks += 2) {
-            const int64_t col = (int64_t)g4 * KM + ks;
-            const float av0 = (row < D && col < D) ? P[row * D + col] : 0.f;
-            const float av1 = (row < D && col + 1 < D) ? P[row * D + col + 1] : 0.f;
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(av0, xs[col * 17 + i16], acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(av1, xs[(col + 1) * 17 + i16], acc1, 0, 0, 0);
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int64_t d = 16 * mt + 4 * g4 + v;
-            if (!(d < D && cvalid)) continue;
-            const float gv = -(acc0[v] + acc1[v]);
-            const float kd = a.ws.scale ? (float)(kick_scale * a.ws.eps[c] * (a.ws.beta ? a.ws.beta[c] : 1.0) *
-                                                  a.ws.scale[d])
-                                        : keps;
-            if (mode & 1) xdst[c * D + d] = xr[m][v];
-            if (mode & 2) pd[c * D + d] = fmaf(kd, gv, pr[m][v]);
-            if (gd) gd[c * D + d] = gv;
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Dense Gaussian, merged transition (D <= 128): one launch per leapfrog step,
 // 16 chains per workgroup of 8 waves, wave w owning M-tile w of g = -P x.
 // P is loaded once per launch into VGPRs as the A operands of
@@ -602,7 +554,7 @@ __global__ __launch_bounds__(256) void k_dense_leapfrog(PlainArgs a, const float
 // x is staged chain-major in LDS for the B operands: the operand layout and
 // MFMA sequence of the fused dense kernel (k = g4 KM + ks, even and odd
 // k-steps in two accumulators), so the gradient is bitwise the one of
-// k_dense_leapfrog and of the fused form.  Lane (i16, g4) of wave w holds
+// k_dense_grad and of the fused form.  Lane (i16, g4) of wave w holds
 // dims 16 w + 4 g4 + v of chain i16.  FIRST also draws the momentum (Philox
 // block 4 w + g4), forms H0 and makes the first half kick; LAST forms H at the
 // trajectory's end, takes the Metropolis decision and writes the accepted
@@ -1231,24 +1183,9 @@ int64_t logreg_nsplit(int64_t N, int64_t C) {
     return want;
 }
 
-static size_t dense_lds(int64_t D) { return (size_t)16 * ((D + 15) / 16) * 17 * sizeof(float); }
-
 template <typename K>
 static void allow_lds(K kernel, size_t lds) {
     if (lds > 65536) (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-}
-
-static hipError_t launch_dense(const PlainArgs& a, const float* xs, float* xd, float* pd, float* gd, int mode,
-                               double ks, hipStream_t s) {
-    const int ntiles = (int)((a.tg.D + 15) / 16);
-    const dim3 grid((unsigned)((a.C + 15) / 16));
-    const size_t lds = dense_lds(a.tg.D);
-    allow_lds(k_dense_leapfrog<16>, lds);
-    if (ntiles <= 4) hipLaunchKernelGGL(k_dense_leapfrog<1>, grid, dim3(256), lds, s, a, xs, xd, pd, gd, mode, ks);
-    else if (ntiles <= 8) hipLaunchKernelGGL(k_dense_leapfrog<2>, grid, dim3(256), lds, s, a, xs, xd, pd, gd, mode, ks);
-    else if (ntiles <= 16) hipLaunchKernelGGL(k_dense_leapfrog<4>, grid, dim3(256), lds, s, a, xs, xd, pd, gd, mode, ks);
-    else hipLaunchKernelGGL(k_dense_leapfrog<16>, grid, dim3(256), lds, s, a, xs, xd, pd, gd, mode, ks);
-    return hipGetLastError();
 }
 
 // largest split count the workspace is sized for (the autotuner tries up to 2x the default)
@@ -1421,7 +1358,7 @@ hipError_t launch_bootstrap(const PlainArgs& a_in, const void* x_src, hipStream_
                                (const float*)a.ws.x, (float*)nullptr, (float*)nullptr, (float*)a.ws.g, 0, 0.0);
         break;
     case HMC_TGT_GAUSS_DENSE:
-        (void)launch_dense(a, (const float*)a.ws.x, nullptr, nullptr, (float*)a.ws.g, 0, 0.0, s);
+        (void)launch_dense_grad(a, (const float*)a.ws.x, nullptr, nullptr, (float*)a.ws.g, 0.0, s);
         break;
     case HMC_TGT_LOGREG:
         if (a.bf16_grad) {
@@ -1461,7 +1398,8 @@ hipError_t launch_leapfrog_step(const PlainArgs& a, double ks, hipStream_t s) {
                                (const float*)a.ws.xq, (float*)a.ws.xq, (float*)a.ws.pq, (float*)a.ws.gq, 3, ks);
         break;
     case HMC_TGT_GAUSS_DENSE:
-        (void)launch_dense(a, (const float*)a.ws.xq, (float*)a.ws.xq, (float*)a.ws.pq, (float*)a.ws.gq, 3, ks, s);
+        hipLaunchKernelGGL(k_drift, elem_grid(a.C * a.tg.D), dim3(256), 0, s, a);
+        (void)launch_dense_grad(a, (const float*)a.ws.xq, nullptr, (float*)a.ws.pq, (float*)a.ws.gq, ks, s);
         break;
     case HMC_TGT_LOGREG:
         if (a.bf16_grad) {
@@ -1635,7 +1573,13 @@ hipError_t launch_plain_transition(const PlainArgs& a, bool copy_proposal, hipSt
     if ((a.tg.kind == HMC_TGT_STD_NORMAL || a.tg.kind == HMC_TGT_GAUSS_DIAG) && launch_elem_transition(a, s))
         return hipGetLastError();
     if (a.tg.kind == HMC_TGT_GAUSS_DENSE && launch_dense_transition(a, s)) return hipGetLastError();
-    if (a.f64) HMC_GROUP_DISPATCH(k_begin, double, a, s);
+    // the dense Gaussian's position alternates between xq and gq: the last step
+    // reads it from xq and leaves the gradient in gq
+    float* const xbuf[2] = {(float*)a.ws.xq, (float*)a.ws.gq};
+    if (a.tg.kind == HMC_TGT_GAUSS_DENSE)
+        hipLaunchKernelGGL(k_begin_drift, dim3((unsigned)((a.C * 64 + 255) / 256)), dim3(256), 0, s, a,
+                           xbuf[(a.L - 1) & 1]);
+    else if (a.f64) HMC_GROUP_DISPATCH(k_begin, double, a, s);
     else HMC_GROUP_DISPATCH(k_begin, float, a, s);
     for (int l = 0; l < a.L; ++l) {
         const bool last = l == a.L - 1;
@@ -1656,9 +1600,9 @@ hipError_t launch_plain_transition(const PlainArgs& a, bool copy_proposal, hipSt
             break;
         case HMC_TGT_GAUSS_DENSE:
             timer_begin(a, s);
-            (void)launch_dense(a, (const float*)a.ws.xq, (float*)a.ws.xq, (float*)a.ws.pq,
-                         last ? (float*)a.ws.gq : nullptr, 3, ks, s);
-            timer_end(a, s, "k_dense_leapfrog");
+            (void)launch_dense_grad(a, xbuf[(a.L - 1 - l) & 1], last ? nullptr : xbuf[(a.L - 2 - l) & 1],
+                                    (float*)a.ws.pq, last ? (float*)a.ws.gq : nullptr, ks, s);
+            timer_end(a, s, "k_dense_grad");
             break;
         case HMC_TGT_LOGREG:
             if (a.bf16_grad) {
