@@ -503,6 +503,18 @@ struct LbLogp {
     static constexpr int LDS = NB * BUF;
 };
 
+// theta = hi + mid + lo in BF16
+__device__ __forceinline__ void lb_split_theta(floatx8 v, bf16x8& hi, bf16x8& mid, bf16x8& lo) {
+    floatx8 r1, r2;
+    hi = pack_bf16(v);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) r1[e] = v[e] - bf16_to_f32((uint16_t)hi[e]);
+    mid = pack_bf16(r1);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) r2[e] = r1[e] - bf16_to_f32((uint16_t)mid[e]);
+    lo = pack_bf16(r2);
+}
+
 template <int KS>
 __device__ __forceinline__ void lr16_logp_body(const PlainArgs& a, const float* __restrict__ xsrc,
                                                int64_t rows_per_split, int nsplit, int blk) {
@@ -529,18 +541,7 @@ __device__ __forceinline__ void lr16_logp_body(const PlainArgs& a, const float* 
         floatx8 v[KS];
         lb_load_theta<KS>(a, xsrc, nullptr, 0, cw + 16 * cs + l16, g, v);
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            floatx8 r1, r2;
-            const bf16x8 h = pack_bf16(v[ks]);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) r1[e] = v[ks][e] - bf16_to_f32((uint16_t)h[e]);
-            const bf16x8 m = pack_bf16(r1);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) r2[e] = r1[e] - bf16_to_f32((uint16_t)m[e]);
-            th[0][cs][ks] = h;
-            th[1][cs][ks] = m;
-            th[2][cs][ks] = pack_bf16(r2);
-        }
+        for (int ks = 0; ks < KS; ++ks) lb_split_theta(v[ks], th[0][cs][ks], th[1][cs][ks], th[2][cs][ks]);
     }
     const int64_t r_begin = (int64_t)split * rows_per_split;
     int64_t r_end = r_begin + rows_per_split;
@@ -674,6 +675,398 @@ __global__ __launch_bounds__(64 * LbLogp<KS>::NW) void k_lr16_logp_pipe(PlainArg
 __global__ __launch_bounds__(256) void k_lr16_lp_sum(PlainArgs a, int nsplit) { lr16_lp_sum_body(a, nsplit, blockIdx.x); }
 
 // ---------------------------------------------------------------------------
+// Few chains: the kernels above give a wave 16 or 32 chains and all rows of its
+// split, so a launch has ceil(C / 256) (ceil(C / 128)) tiles x at most 8 splits
+// of workgroups -- 8 on 256 CUs at 200 chains, and each walks its rows alone, at
+// the rate one CU pulls X and X^T.  Here a workgroup of 8 waves owns 16 CS
+// chains and one split, and its waves share the work of a row: in a stage of NS
+// sub-tiles the waves form S and the residuals of 16-row halves (wave w those of
+// chain tile w % CS); the packed residuals go through LDS; after a barrier wave
+// w accumulates dim tiles w, w + 8, .. of G^T over the stage's sub-tiles in
+// their order.  Every output sees the MFMAs it sees above, in the same order
+// (the split count is the same too): the partials are bitwise the same.
+//
+// X alone is copied global -> LDS (contiguous rows; the 64-byte pieces of X^T
+// would take a cache line each), NBUF - 1 stages ahead, and read there by rows
+// for S and transposed (ds_read_b64_tr_b16) for G^T; 16-byte slots are swizzled
+// by f(row) = 2 (row & 3) + ((row >> 3) & 1), distinct over the 8 rows of a row
+// phase and even-distinct over the 4 of a transposed one.
+// ---------------------------------------------------------------------------
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+template <int KS, int CS>
+struct LbFew {
+    static constexpr int NW = 8;
+    static constexpr int DP = 32 * KS, RB = 2 * DP;                      // dims and bytes of a row
+    static constexpr int NS = KS <= 2 ? 8 : (KS <= 6 ? 4 : 2);           // sub-tiles per stage
+    static constexpr int XB = NS * LB_RS * RB;                           // bytes of a stage
+    static constexpr int BUF = XB + 256;                                 // and its labels
+    static constexpr int RES = NS * CS * 1024;                           // bytes of a stage's residuals
+    static constexpr int NBUF = 4 * BUF + RES <= 160 * 1024 ? 4 : (3 * BUF + RES <= 160 * 1024 ? 3 : 2);
+    static constexpr int XI = XB / 1024;                                 // 1 KB copy blocks of a stage
+    static constexpr int J = XI / NW + 1;                                // copies per wave, labels included
+    static constexpr int NH = 2 * NS;                                    // 16-row halves of a stage
+    static constexpr int NT = 2 * KS, TPW = (NT + NW - 1) / NW;          // dim tiles, per wave
+    static_assert(XI % NW == 0, "copies must split evenly over the waves");
+};
+__device__ __forceinline__ int lb_few_swz(int row, int slots) {
+    return (((row & 3) << 1) | ((row >> 3) & 1)) & (slots - 1 < 7 ? slots - 1 : 7);
+}
+// Copy of the stage at xsrc (labels ysrc) into buf.  Only the first `rows` rows
+// belong to the split: later ones repeat the first and are never used.
+template <int KS, int CS>
+__device__ __forceinline__ void lb_few_copy(const char* xsrc, const uint8_t* ysrc, int rows, uint8_t* __restrict__ buf,
+                                            int w, int lane) {
+    using P = LbFew<KS, CS>;
+    constexpr int SR = 4 * KS;
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+#pragma unroll
+    for (int k = 0; k < P::J - 1; ++k) {
+        const int i = w + P::NW * k, q = i * 64 + ln;
+        const int row = q / SR, c = (q % SR) ^ lb_few_swz(row, SR);
+        const uint32_t off = (uint32_t)((row < rows ? row : 0) * P::RB + 16 * c);
+        __builtin_amdgcn_global_load_lds((const void*)(xsrc + off), (lds_void_t*)(buf + i * 1024), 16, 0, 0);
+    }
+    __builtin_amdgcn_global_load_lds((const void*)(ysrc + (4 * ln < rows ? 4 * ln : 0)), (lds_void_t*)(buf + P::XB), 4,
+                                     0, 0);
+}
+
+// Four dims d0 .. d0 + 3 (d0 < D) of a row of D >= 4 floats by one 16-byte load at
+// whatever alignment, moved back inside the row where it would run past its end
+// (lb_row4), and the dims it was asked for out of it, zeros past D (lb_pick4).
+struct __attribute__((packed, aligned(4))) f32x4u { floatx4 v; };
+__device__ __forceinline__ floatx4 lb_row4(const float* __restrict__ row, int d0, int D) {
+    return ((const f32x4u*)(row + (d0 + 4 <= D ? d0 : D - 4)))->v;
+}
+__device__ __forceinline__ floatx4 lb_pick4(floatx4 v, int d0, int D) {
+    const int sh = d0 + 4 <= D ? 0 : d0 + 4 - D;
+    floatx4 r;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        float e = v[j];
+#pragma unroll
+        for (int k = 1; j + k < 4; ++k) e = sh == k ? v[j + k] : e;
+        r[j] = d0 + j < D ? e : 0.f;
+    }
+    return r;
+}
+// theta (drifted when drift) of chains c0 .. c0 + NC - 1, loaded once by the
+// workgroup: unit u = 512 k + thread is dims 4 (u % (8 KS)) of chain u / (8 KS).
+// (Every wave loading the rows for itself had cost a third of the launch at D =
+// 150, where rows are read by single floats.)
+template <int KS, int NC>
+struct LbTheta {
+    static constexpr int NU = (NC * 8 * KS + 511) / 512;
+    floatx4 v[NU];
+    __device__ __forceinline__ void load(const PlainArgs& a, const float* __restrict__ x, const float* __restrict__ p,
+                                         int drift, int64_t c0) {
+        const int D = (int)a.tg.D;
+        floatx4 pv[NU];
+        float eps[NU];
+        if (D >= 4) {
+#pragma unroll
+            for (int k = 0; k < NU; ++k) {
+                const int64_t cc = c0 + chain(k) < a.C ? c0 + chain(k) : 0;
+                const int d0 = dim(k) < D ? dim(k) : 0;
+                v[k] = lb_row4(x + cc * D, d0, D);
+                if (drift) {
+                    pv[k] = lb_row4(p + cc * D, d0, D);
+                    eps[k] = (float)a.ws.eps[cc];
+                }
+            }
+        } else {
+            asm volatile("" ::: "memory");        // keeps the two kinds of loads apart
+#pragma unroll
+            for (int k = 0; k < NU; ++k) {
+                const int64_t cc = c0 + chain(k) < a.C ? c0 + chain(k) : 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    // as lb_row4 would deliver them: d0 = 0, moved back by 4 - D
+                    const int d = j - (4 - D) > 0 ? j - (4 - D) : 0;
+                    v[k][j] = x[cc * D + d];
+                    if (drift) pv[k][j] = p[cc * D + d];
+                }
+                if (drift) eps[k] = (float)a.ws.eps[cc];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < NU; ++k) {
+            const bool ok = c0 + chain(k) < a.C;
+            const int d0 = dim(k);
+            v[k] = lb_pick4(v[k], d0, D);
+            if (drift) {
+                pv[k] = lb_pick4(pv[k], d0, D);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[k][j] = fmaf(eps[k], pv[k][j], v[k][j]);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[k][j] = ok && d0 + j < D ? v[k][j] : 0.f;
+        }
+    }
+    // the chain and first dim of this thread's unit k (chain NC or more: none)
+    __device__ __forceinline__ int chain(int k) const { return (512 * k + (int)threadIdx.x) / (8 * KS); }
+    __device__ __forceinline__ int dim(int k) const { return 4 * ((512 * k + (int)threadIdx.x) % (8 * KS)); }
+};
+
+template <int KS, int CS>
+__global__ __launch_bounds__(512) void k_lr16_grad_few(PlainArgs a, const float* __restrict__ xsrc,
+                                                       const float* __restrict__ psrc, int drift,
+                                                       int64_t rows_per_split, int nsplit) {
+    using P = LbFew<KS, CS>;
+    constexpr int RB = P::RB, NS = P::NS, XB = P::XB, BUF = P::BUF, NBUF = P::NBUF, J = P::J, NH = P::NH, NT = P::NT, TPW = P::TPW,
+                  NW = P::NW, NG = NW / CS, HW = (NH + NG - 1) / NG;
+    extern __shared__ __align__(16) uint8_t ldsb[];
+    // NBUF stages of X, then the residuals [NS][CS][64 lanes][16 bytes]
+    const int64_t D = a.tg.D, C = a.C, NP = (a.tg.N + LB_RS - 1) / LB_RS * LB_RS;
+    const int ntile = (int)((C + 16 * CS - 1) / (16 * CS));
+    int tile, split;
+    lb_map(blockIdx.x, ntile, nsplit, &tile, &split);
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, g = lane >> 4;
+    const int64_t cw = (int64_t)tile * (16 * CS);
+    const int wcs = w % CS, wg = w / CS;                  // chain tile and half group of S
+
+    const int64_t r_begin = (int64_t)split * rows_per_split;
+    int64_t r_end = r_begin + rows_per_split;
+    if (r_end > NP) r_end = NP;
+    const int nsub = r_begin < r_end ? (int)((r_end - r_begin) / LB_RS) : 0;
+    const int nst = (nsub + NS - 1) / NS;
+    const char* xs = (const char*)a.ws.xp + r_begin * RB;
+    const uint8_t* ys = (const uint8_t*)a.ws.yp + r_begin;
+    auto copy_in = [&](int t, uint8_t* __restrict__ dst) {
+        const int left = (nsub - NS * t) * LB_RS;
+        lb_few_copy<KS, CS>(xs + (int64_t)t * XB, ys + t * (NS * LB_RS), left < NS * LB_RS ? left : NS * LB_RS, dst, w, lane);
+    };
+    // theta of the workgroup's chains through the last stage buffer (free until the
+    // first stage has passed its barrier) as B operands
+    bf16x8 thb[KS];
+    auto prologue = [&](uint8_t* __restrict__ tb, uint8_t* __restrict__ dst) {
+        constexpr int TS = RB + 16;                       // bytes of a chain's row there
+        LbTheta<KS, 16 * CS> th;
+        th.load(a, xsrc, psrc, drift, cw);
+#pragma unroll
+        for (int t = 0; t < NBUF - 1; ++t)
+            if (t < nst) copy_in(t, dst + t * BUF);
+#pragma unroll
+        for (int k = 0; k < th.NU; ++k)
+            if (th.chain(k) < 16 * CS) *(uint2*)(tb + th.chain(k) * TS + 2 * th.dim(k)) = pack4_bf16(th.v[k]);
+        lds_barrier();
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) thb[ks] = *(const bf16x8*)(tb + (16 * wcs + l16) * TS + 64 * ks + 16 * g);
+    };
+    prologue(ldsb + (NBUF - 1) * BUF, ldsb);
+    floatx4 gacc[CS][TPW];
+#pragma unroll
+    for (int cs = 0; cs < CS; ++cs)
+#pragma unroll
+        for (int j = 0; j < TPW; ++j) gacc[cs][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // offsets in a sub-tile: row fragments of half mt (even / odd k-step), the transposed
+    // blocks of the wave's dim tiles
+    uint32_t xo[2][2], to[TPW];
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+        const int row = 8 * (l16 >> 2) + 4 * mt + (l16 & 3), f = lb_few_swz(row, 4 * KS);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) xo[mt][e] = (uint32_t)(row * RB + 16 * ((g + 4 * e) ^ f));
+    }
+    {
+        const int row = 8 * g + (l16 >> 2), f = lb_few_swz(row, 4 * KS);
+#pragma unroll
+        for (int j = 0; j < TPW; ++j) {
+            const int nt = w + NW * j < NT ? w + NW * j : NT - 1;
+            to[j] = (uint32_t)(row * RB + 16 * ((2 * nt + ((l16 & 3) >> 1)) ^ f) + 8 * (l16 & 1));
+        }
+    }
+    // one stage; the copy target, the buffer read and the residuals are distinct, which
+    // the restrict qualifiers tell the compiler: the LDS reads wait for no copy in flight
+    auto stage = [&](int t, uint8_t* __restrict__ dst, const uint8_t* __restrict__ xb, uint8_t* __restrict__ rbuf) {
+        // stage t complete: at most the copies of the stages after it outstanding
+        if (NBUF >= 4 && t + 2 < nst) wait_vmcnt<2 * J>();
+        else if (NBUF >= 3 && t + 1 < nst) wait_vmcnt<J>();
+        else wait_vmcnt<0>();
+        lds_barrier();
+        if (t + NBUF - 1 < nst) copy_in(t + NBUF - 1, dst);
+        const int ns = nsub - NS * t < NS ? nsub - NS * t : NS;
+#pragma unroll
+        for (int u = 0; u < HW; ++u) {
+            const int h = wg + NG * u;                    // uniform over the wave
+            if (h < 2 * ns) {
+                const uint8_t* xh = xb + (h >> 1) * (LB_RS * RB);
+                const uint32_t o0 = (h & 1) ? xo[1][0] : xo[0][0], o1 = (h & 1) ? xo[1][1] : xo[0][1];
+                bf16x8 xa[KS];
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) xa[ks] = *(const bf16x8*)(xh + ((ks & 1) ? o1 : o0) + 128 * (ks >> 1));
+                floatx4 sacc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks)
+                    sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[ks], thb[ks], sacc, 0, 0, 0);
+                // every fragment read first (one LDS latency), then the chain of MFMAs
+                __builtin_amdgcn_sched_group_barrier(0x100, KS, 0);
+                __builtin_amdgcn_sched_group_barrier(0x008, KS, 0);
+                // labels of the lane's rows 8 g + 4 mt .. + 3
+                const uint32_t yw = *(const uint32_t*)(xb + XB + LB_RS * (h >> 1) + 8 * g + 4 * (h & 1));
+                floatx4 r;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) r[v] = (float)((yw >> (8 * v)) & 0xffu) - sigmoid_hw(sacc[v]);
+                *(uint2*)(rbuf + ((((h >> 1) * CS + wcs) * 64 + lane) * 16 + 8 * (h & 1))) = pack4_bf16(r);
+            }
+        }
+        lds_barrier();
+        // a wave's tiles past NT repeat the last one (not stored)
+        auto gsub = [&](int s) {
+            bf16x8 ra[CS], bx[TPW];
+#pragma unroll
+            for (int cs = 0; cs < CS; ++cs) ra[cs] = *(const bf16x8*)(rbuf + ((s * CS + cs) * 64 + lane) * 16);
+#pragma unroll
+            for (int j = 0; j < TPW; ++j) {
+                const uint8_t* p = xb + s * (LB_RS * RB) + to[j];
+                const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+                const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * RB));
+                bx[j] = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
+            }
+#pragma unroll
+            for (int j = 0; j < TPW; ++j)
+#pragma unroll
+                for (int cs = 0; cs < CS; ++cs)
+                    gacc[cs][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ra[cs], bx[j], gacc[cs][j], 0, 0, 0);
+        };
+        if (ns == NS) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s) gsub(s);
+        } else {
+            for (int s = 0; s < ns; ++s) gsub(s);
+        }
+    };
+    for (int t = 0; t < nst; ++t)
+        stage(t, ldsb + ((t + NBUF - 1) % NBUF) * BUF, ldsb + (t % NBUF) * BUF, ldsb + NBUF * BUF);
+#pragma unroll
+    for (int cs = 0; cs < CS; ++cs)
+#pragma unroll
+        for (int j = 0; j < TPW; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int64_t c = cw + 16 * cs + 4 * g + v;
+                const int64_t d = 16 * (w + NW * j) + l16;
+                if (c < C && d < D) a.ws.part_g[((int64_t)split * C + c) * D + d] = gacc[cs][j][v];
+            }
+}
+
+// The accurate log-probability for few chains, likewise: a workgroup owns 16
+// chains and one split, the waves form the logits and the FP32 sums of 4 rows'
+// terms of the stage's halves, and wave 0 adds those in FP64 in the row order of
+// the kernel above (bitwise the same partials).
+template <int KS>
+__global__ __launch_bounds__(512) void k_lr16_logp_few(PlainArgs a, const float* __restrict__ xsrc,
+                                                       int64_t rows_per_split, int nsplit) {
+    using P = LbFew<KS, 1>;
+    constexpr int RB = P::RB, NS = P::NS, XB = P::XB, BUF = P::BUF, NBUF = P::NBUF, J = P::J, NH = P::NH, NW = P::NW,
+                  HW = (NH + NW - 1) / NW;
+    extern __shared__ __align__(16) uint8_t ldsb[];
+    // NBUF stages of X, then the terms [2][NH][64]
+    const int64_t N = a.tg.N, C = a.C, NP = (N + LB_RS - 1) / LB_RS * LB_RS;
+    const int ntile = (int)((C + 15) / 16);
+    int tile, split;
+    lb_map(blockIdx.x, ntile, nsplit, &tile, &split);
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, g = lane >> 4;
+    const int64_t c = (int64_t)tile * 16 + l16;
+    const int64_t r_begin = (int64_t)split * rows_per_split;
+    int64_t r_end = r_begin + rows_per_split;
+    if (r_end > NP) r_end = NP;
+    const int nsub = r_begin < r_end ? (int)((r_end - r_begin) / LB_RS) : 0;
+    const int nst = (nsub + NS - 1) / NS;
+    const char* xs = (const char*)a.ws.xp + r_begin * RB;
+    const uint8_t* ys = (const uint8_t*)a.ws.yp + r_begin;
+    auto copy_in = [&](int t, uint8_t* __restrict__ dst) {
+        const int left = (nsub - NS * t) * LB_RS;
+        lb_few_copy<KS, 1>(xs + (int64_t)t * XB, ys + t * (NS * LB_RS), left < NS * LB_RS ? left : NS * LB_RS, dst, w, lane);
+    };
+    bf16x8 th[3][KS];
+    auto prologue = [&](uint8_t* __restrict__ tb, uint8_t* __restrict__ dst) {
+        constexpr int TS = 2 * RB + 16;                   // FP32 theta through the last stage buffer
+        LbTheta<KS, 16> tv;
+        tv.load(a, xsrc, nullptr, 0, (int64_t)tile * 16);
+#pragma unroll
+        for (int t = 0; t < NBUF - 1; ++t)
+            if (t < nst) copy_in(t, dst + t * BUF);
+#pragma unroll
+        for (int k = 0; k < tv.NU; ++k)
+            if (tv.chain(k) < 16) *(floatx4*)(tb + tv.chain(k) * TS + 4 * tv.dim(k)) = tv.v[k];
+        lds_barrier();
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const float* r = (const float*)(tb + l16 * TS) + 32 * ks + 8 * g;
+            const floatx4 u0 = *(const floatx4*)r, u1 = *(const floatx4*)(r + 4);
+            lb_split_theta(floatx8{u0[0], u0[1], u0[2], u0[3], u1[0], u1[1], u1[2], u1[3]}, th[0][ks], th[1][ks],
+                           th[2][ks]);
+        }
+    };
+    prologue(ldsb + (NBUF - 1) * BUF, ldsb);
+    uint32_t xo[2][2];
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+        const int row = 8 * (l16 >> 2) + 4 * mt + (l16 & 3), f = lb_few_swz(row, 4 * KS);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) xo[mt][e] = (uint32_t)(row * RB + 16 * ((g + 4 * e) ^ f));
+    }
+    double lp = 0.0;
+    auto stage = [&](int t, uint8_t* __restrict__ dst, const uint8_t* __restrict__ xb, float* __restrict__ tbuf) {
+        if (NBUF >= 4 && t + 2 < nst) wait_vmcnt<2 * J>();
+        else if (NBUF >= 3 && t + 1 < nst) wait_vmcnt<J>();
+        else wait_vmcnt<0>();
+        lds_barrier();
+        if (t + NBUF - 1 < nst) copy_in(t + NBUF - 1, dst);
+        // the sums of stage t - 1 (its terms were complete at the barrier)
+        auto add = [&](int tp) {
+            const int np = nsub - NS * tp < NS ? nsub - NS * tp : NS;
+            for (int h = 0; h < 2 * np; ++h) lp += (double)tbuf[((tp & 1) * NH + h) * 64 + lane];
+        };
+        if (w == 0 && t > 0) add(t - 1);
+        const int ns = nsub - NS * t < NS ? nsub - NS * t : NS;
+#pragma unroll
+        for (int u = 0; u < HW; ++u) {
+            const int h = w + NW * u;
+            if (h < 2 * ns) {
+                const uint8_t* xh = xb + (h >> 1) * (LB_RS * RB);
+                const uint32_t o0 = (h & 1) ? xo[1][0] : xo[0][0], o1 = (h & 1) ? xo[1][1] : xo[0][1];
+                floatx4 sacc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    const bf16x8 ax = *(const bf16x8*)(xh + ((ks & 1) ? o1 : o0) + 128 * (ks >> 1));
+#pragma unroll
+                    for (int term = 2; term >= 0; --term)
+                        sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ax, th[term][ks], sacc, 0, 0, 0);
+                }
+                const int64_t row0 = r_begin + (int64_t)LB_RS * (NS * t + (h >> 1)) + 8 * g + 4 * (h & 1);
+                const bool whole = row0 + 4 <= N;
+                const uint32_t yw = *(const uint32_t*)(xb + XB + LB_RS * (h >> 1) + 8 * g + 4 * (h & 1));
+                float t4 = 0.f;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float s = sacc[v];
+                    const float y = (float)((yw >> (8 * v)) & 0xffu);
+                    const float tv = fmaf(y, s, -softplus_hw(s));
+                    t4 += (whole || row0 + v < N) ? tv : 0.f;
+                }
+                tbuf[((t & 1) * NH + h) * 64 + lane] = t4;
+            }
+        }
+        if (t + 1 == nst) {
+            lds_barrier();
+            if (w == 0) add(t);
+        }
+    };
+    for (int t = 0; t < nst; ++t)
+        stage(t, ldsb + ((t + NBUF - 1) % NBUF) * BUF, ldsb + (t % NBUF) * BUF, (float*)(ldsb + NBUF * BUF));
+    if (w != 0) return;
+    lp += __shfl_xor(lp, 16, 64);
+    lp += __shfl_xor(lp, 32, 64);
+    if (g == 0 && c < C) a.ws.part_lp[(int64_t)split * C + c] = lp;
+}
+
+// ---------------------------------------------------------------------------
 // Several requests in one launch (the serving form): job j owns blocks
 // begin[k] .. begin[k] + nblk[k] - 1 of the grid of kernel kind k; its
 // arguments are copied out of the device job table into registers, and the
@@ -785,18 +1178,46 @@ hipError_t launch_pad_bf16(const PlainArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <int KS, int CS>
+static hipError_t lb_few_launch(const PlainArgs& a, const float* x, const float* p, int drift, int nsplit,
+                                int64_t rows, hipStream_t s) {
+    using P = LbFew<KS, CS>;
+    constexpr int lds = P::NBUF * P::BUF + P::RES;
+    static_assert((P::NBUF - 1) * P::BUF + 16 * CS * (P::RB + 16) <= lds, "theta's staging");
+    static_assert(lds <= 160 * 1024, "LDS");
+    const int64_t ntile = (a.C + 16 * CS - 1) / (16 * CS);
+    if (lds > 65536)
+        (void)hipFuncSetAttribute((const void*)k_lr16_grad_few<KS, CS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    hipLaunchKernelGGL((k_lr16_grad_few<KS, CS>), dim3((unsigned)(ntile * nsplit)), dim3(512), lds, s, a, x, p, drift,
+                       rows, nsplit);
+    return hipGetLastError();
+}
+
 template <int KS>
 static hipError_t lb_grad_k(const PlainArgs& a, const float* x, const float* p, int drift, hipStream_t s) {
     using P = LbGrad<KS>;
     const int ntile = (int)((a.C + P::CT - 1) / P::CT);
     const int nsplit = lb_grad_nsplit_t(a);
     const int64_t NP = (a.tg.N + LB_RS - 1) / LB_RS * LB_RS;
+    const int64_t rows = rows_for(NP, nsplit);
+    // The few-chain kernel, with as few chains per workgroup as lets its workgroups
+    // (one per CU) run in one round, or up to D = 256 in one and a half: a round of
+    // 64 chains takes half the time of the 256-chain kernel's, which any number of
+    // chains up to a full round takes (beyond D = 256, two thirds of the 128-chain
+    // one's).  Per gradient and its partial sum: 20011 x 150, 200 chains 140 -> 32 us;
+    // 30000 x 250, 1000 chains 255 -> 76, 2000 chains 260 -> 115, 3000 chains 265 ->
+    // 214; 30000 x 512, 2048 chains 274 -> 195.  Past the line: 50000 x 256, 4000
+    // chains 350 in two rounds against 357; 30000 x 512, 3000 chains 342 against 293.
+    auto blocks = [&](int cs) { return (a.C + 16 * cs - 1) / (16 * cs) * nsplit; };
+    if (blocks(1) <= 256) return lb_few_launch<KS, 1>(a, x, p, drift, nsplit, rows, s);
+    if (blocks(2) <= 256) return lb_few_launch<KS, 2>(a, x, p, drift, nsplit, rows, s);
+    if (blocks(4) <= (KS <= 8 ? 384 : 256)) return lb_few_launch<KS, 4>(a, x, p, drift, nsplit, rows, s);
     const size_t lds = (size_t)P::LDS;
     if (lds > 65536)
         (void)hipFuncSetAttribute((const void*)k_lr16_grad_pipe<KS>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)lds);
     hipLaunchKernelGGL(k_lr16_grad_pipe<KS>, dim3((unsigned)(ntile * nsplit)), dim3(64 * P::NW), lds, s, a, x, p,
-                       drift, rows_for(NP, nsplit), nsplit);
+                       drift, rows, nsplit);
     return hipGetLastError();
 }
 
@@ -806,6 +1227,22 @@ static hipError_t lb_logp_k(const PlainArgs& a, const float* x, hipStream_t s) {
     const int ntile = (int)((a.C + P::CT - 1) / P::CT);
     const int nsplit = lb_logp_nsplit(a.tg.N, a.C, a.tg.D);
     const int64_t NP = (a.tg.N + LB_RS - 1) / LB_RS * LB_RS;
+    // Up to two rounds of 16-chain workgroups (four where the three terms of theta are
+    // few) against the kernel below, whole transitions less the gradients: 20011 x
+    // 150, 200 chains 134 -> 47 us; 30000 x 250, 1000 chains (504 workgroups) 209 -> 161,
+    // 2000 chains (1000) 214 -> 301; 40000 x 60, 1500 chains (752) 177 -> 101.
+    if ((a.C + 15) / 16 * nsplit <= (KS <= 2 ? 1024 : 512)) {
+        using F = LbFew<KS, 1>;
+        constexpr int flds = F::NBUF * F::BUF + 2 * F::NH * 64 * 4;
+        static_assert((F::NBUF - 1) * F::BUF + 16 * (2 * F::RB + 16) <= flds, "theta's staging");
+        static_assert(flds <= 160 * 1024, "LDS");
+        if (flds > 65536)
+            (void)hipFuncSetAttribute((const void*)k_lr16_logp_few<KS>, hipFuncAttributeMaxDynamicSharedMemorySize, flds);
+        hipLaunchKernelGGL(k_lr16_logp_few<KS>, dim3((unsigned)((a.C + 15) / 16 * nsplit)), dim3(512), flds, s, a, x,
+                           rows_for(NP, nsplit), nsplit);
+        hipLaunchKernelGGL(k_lr16_lp_sum, dim3((unsigned)((a.C + 255) / 256)), dim3(256), 0, s, a, nsplit);
+        return hipGetLastError();
+    }
     const size_t lds = (size_t)P::LDS;
     if (lds > 65536)
         (void)hipFuncSetAttribute((const void*)k_lr16_logp_pipe<KS>, hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -1049,19 +1049,20 @@ __global__ __launch_bounds__(256) void k_lr32_boot(PlainArgs a, const float* __r
     if (cv && q == 0) a.ws.part_lp[(int64_t)split * C + c] = lp;
 }
 
-// Sum of p[s * stride], s = 0 .. n - 1, in that order, with up to 32 loads in
-// flight (a load per add waits for each: 64 splits would cost 64 L2 latencies).
-template <typename T>
+// Sum of p[s * stride], s = 0 .. n - 1, in that order, with U loads in flight (a
+// load per add waits for each: 64 splits would cost 64 L2 latencies).
+template <int U, typename T>
 __device__ __forceinline__ T split_sum(const T* __restrict__ p, int64_t stride, int n) {
-    T sum = (T)0;
+    T sum = T{};
     int s0 = 0;
-    for (; s0 + 32 <= n; s0 += 32) {
-        T v[32];
+    if constexpr (U > 8)
+        for (; s0 + U <= n; s0 += U) {
+            T v[U];
 #pragma unroll
-        for (int k = 0; k < 32; ++k) v[k] = p[(int64_t)(s0 + k) * stride];
+            for (int k = 0; k < U; ++k) v[k] = p[(int64_t)(s0 + k) * stride];
 #pragma unroll
-        for (int k = 0; k < 32; ++k) sum += v[k];
-    }
+            for (int k = 0; k < U; ++k) sum += v[k];
+        }
     for (; s0 < n; s0 += 8) {
         T v[8];
 #pragma unroll
@@ -1074,34 +1075,44 @@ __device__ __forceinline__ T split_sum(const T* __restrict__ p, int64_t stride, 
 }
 
 // drift (same fmaf as the partial kernel), sum the split partials in split
-// order, add the prior gradient, kick.  Bound by latency and the partials' bytes.
+// order, add the prior gradient, kick.  V consecutive elements of a row per
+// thread: 1, or 4 by 16-byte accesses (D a multiple of 4) where the elements fill
+// the chip anyway and the launch is bound by the partials' bytes (8192 x 256, 8
+// splits: 17.0 us; 23.9 by single elements with 32 loads in flight).
+template <int V>
 __device__ __forceinline__ void finish_body(const PlainArgs& a, float* __restrict__ xd, float* __restrict__ pd,
                                             float* __restrict__ gd, int nsplit, int drift, int kick,
                                             double kick_scale, int want_logp, int64_t blk, int64_t nblk) {
+    typedef float vec __attribute__((ext_vector_type(V)));
     const int64_t D = a.tg.D, C = a.C;
     const int64_t n = C * D;
-    for (int64_t i = blk * blockDim.x + threadIdx.x; i < n; i += nblk * blockDim.x) {
+    for (int64_t q = blk * blockDim.x + threadIdx.x; q < n / V; q += nblk * blockDim.x) {
+        const int64_t i = V * q;
         const int64_t c = n <= 0x7fffffff ? (int64_t)((uint32_t)i / (uint32_t)D) : i / D;
-        float x = xd[i];
-        const float p = (drift || kick) ? pd[i] : 0.f;
+        vec x = *(const vec*)(xd + i);
+        const vec p = (drift || kick) ? *(const vec*)(pd + i) : vec{};
         const double eps = a.ws.eps[c], bt = a.ws.beta ? a.ws.beta[c] : 1.0;
-        const double sd = a.ws.scale ? a.ws.scale[i - c * D] : 1.0;
-        const float gsum = split_sum(a.ws.part_g + i, n, nsplit);
-        if (drift) {
-            x = fmaf(a.ws.scale ? (float)(eps * sd) : (float)eps, p, x);
-            xd[i] = x;
+        const vec gsum = split_sum<V == 1 ? 32 : 8>((const vec*)(a.ws.part_g + i), n / V, nsplit);
+        vec pn, gv;
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            const double sd = a.ws.scale ? a.ws.scale[i + j - c * D] : 1.0;
+            if (drift) x[j] = fmaf(a.ws.scale ? (float)(eps * sd) : (float)eps, p[j], x[j]);
+            gv[j] = gsum[j] - x[j] * (float)a.tg.inv_var;
+            pn[j] = fmaf((float)(kick_scale * eps * bt * sd), gv[j], p[j]);
         }
-        const float gv = gsum - x * (float)a.tg.inv_var;
-        if (kick) pd[i] = fmaf((float)(kick_scale * eps * bt * sd), gv, p);
-        if (gd) gd[i] = gv;
-        if (want_logp && i - c * D == 0) a.ws.lpq[c] = split_sum(a.ws.part_lp + c, C, nsplit);
+        if (drift) *(vec*)(xd + i) = x;
+        if (kick) *(vec*)(pd + i) = pn;
+        if (gd) *(vec*)(gd + i) = gv;
+        if (want_logp && i - c * D == 0) a.ws.lpq[c] = split_sum<32>(a.ws.part_lp + c, C, nsplit);
     }
 }
 
+template <int V>
 __global__ __launch_bounds__(256) void k_logreg_finish(PlainArgs a, float* __restrict__ xd, float* __restrict__ pd,
                                                        float* __restrict__ gd, int nsplit, int drift, int kick,
                                                        double kick_scale, int want_logp) {
-    finish_body(a, xd, pd, gd, nsplit, drift, kick, kick_scale, want_logp, blockIdx.x, gridDim.x);
+    finish_body<V>(a, xd, pd, gd, nsplit, drift, kick, kick_scale, want_logp, blockIdx.x, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1132,7 +1143,7 @@ __global__ __launch_bounds__(256) void k_finish_multi(const Lr16Job* __restrict_
     const int j = lr16_job_of(jobs, njobs, LR16_KIND_FINISH, blockIdx.x, &lb);
     if (j < 0) return;
     const PlainArgs a = jobs[j].a;
-    finish_body(a, (float*)a.ws.xq, (float*)a.ws.pq, last ? (float*)a.ws.gq : nullptr, jobs[j].nsplit_g, 1, 1,
+    finish_body<1>(a, (float*)a.ws.xq, (float*)a.ws.pq, last ? (float*)a.ws.gq : nullptr, jobs[j].nsplit_g, 1, 1,
                 last ? 0.5 : 1.0, 0, lb, jobs[j].nblk[LR16_KIND_FINISH]);
 }
 
@@ -1228,6 +1239,17 @@ static int launch_lr32_boot(const PlainArgs& a, hipStream_t s) {
     return nsplit;
 }
 
+static void launch_finish(const PlainArgs& a, float* x, float* p, float* gd, int nsplit, int drift, int kick,
+                          double ks, int want_logp, hipStream_t s) {
+    const int64_t n = a.C * a.tg.D;
+    if (a.tg.D % 4 == 0 && n >= (1 << 19))
+        hipLaunchKernelGGL(k_logreg_finish<4>, elem_grid(n / 4), dim3(256), 0, s, a, x, p, gd, nsplit, drift, kick, ks,
+                           want_logp);
+    else
+        hipLaunchKernelGGL(k_logreg_finish<1>, elem_grid(n), dim3(256), 0, s, a, x, p, gd, nsplit, drift, kick, ks,
+                           want_logp);
+}
+
 // One FP32 gradient evaluation of logistic regression at x (drifted in place
 // first when drift), kicking p when kick, the gradient into gd if not null and
 // the data part of logp into lpq when want_logp: the split partials, then their
@@ -1240,8 +1262,7 @@ static hipError_t launch_logreg(const PlainArgs& a, float* x, float* p, float* g
     const hipError_t e = launch_lr32_grad(a, x, p, drift, want_logp, nsplit, rows, s);
     timer_end(a, s, "k_lr32_step");
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_logreg_finish, elem_grid(a.C * a.tg.D), dim3(256), 0, s, a, x, p, gd, nsplit, drift, kick,
-                       ks, want_logp);
+    launch_finish(a, x, p, gd, nsplit, drift, kick, ks, want_logp, s);
     return hipGetLastError();
 }
 
@@ -1363,14 +1384,12 @@ hipError_t launch_bootstrap(const PlainArgs& a_in, const void* x_src, hipStream_
     case HMC_TGT_LOGREG:
         if (a.bf16_grad) {
             (void)launch_lr16_grad(a, (const float*)a.ws.x, nullptr, 0, s);
-            hipLaunchKernelGGL(k_logreg_finish, elem_grid(a.C * a.tg.D), dim3(256), 0, s, a, (float*)a.ws.x,
-                               (float*)nullptr, (float*)a.ws.g, lb_grad_nsplit_t(a), 0, 0, 0.0, 0);
+            launch_finish(a, (float*)a.ws.x, nullptr, (float*)a.ws.g, lb_grad_nsplit_t(a), 0, 0, 0.0, 0, s);
             (void)launch_lr16_logp(a, (const float*)a.ws.x, s);
         } else {
             if (a.tg.D <= 32) {
                 const int nsplit = launch_lr32_boot(a, s);
-                hipLaunchKernelGGL(k_logreg_finish, elem_grid(a.C * a.tg.D), dim3(256), 0, s, a, (float*)a.ws.x,
-                                   (float*)nullptr, (float*)a.ws.g, nsplit, 0, 0, 0.0, 1);
+                launch_finish(a, (float*)a.ws.x, nullptr, (float*)a.ws.g, nsplit, 0, 0, 0.0, 1, s);
             } else {
                 (void)launch_logreg(a, (float*)a.ws.x, nullptr, (float*)a.ws.g, 0, 0, 0.0, 1, s);
             }
@@ -1404,8 +1423,7 @@ hipError_t launch_leapfrog_step(const PlainArgs& a, double ks, hipStream_t s) {
     case HMC_TGT_LOGREG:
         if (a.bf16_grad) {
             (void)launch_lr16_grad(a, (const float*)a.ws.xq, (const float*)a.ws.pq, 1, s);
-            hipLaunchKernelGGL(k_logreg_finish, elem_grid(a.C * a.tg.D), dim3(256), 0, s, a, (float*)a.ws.xq,
-                               (float*)a.ws.pq, (float*)a.ws.gq, lb_grad_nsplit_t(a), 1, 1, ks, 0);
+            launch_finish(a, (float*)a.ws.xq, (float*)a.ws.pq, (float*)a.ws.gq, lb_grad_nsplit_t(a), 1, 1, ks, 0, s);
             (void)launch_lr16_logp(a, (const float*)a.ws.xq, s);
             break;
         }
@@ -1609,9 +1627,8 @@ hipError_t launch_plain_transition(const PlainArgs& a, bool copy_proposal, hipSt
                 timer_begin(a, s);
                 (void)launch_lr16_grad(a, (const float*)a.ws.xq, (const float*)a.ws.pq, 1, s);
                 timer_end(a, s, "k_lr16_grad");
-                hipLaunchKernelGGL(k_logreg_finish, elem_grid(a.C * a.tg.D), dim3(256), 0, s, a, (float*)a.ws.xq,
-                                   (float*)a.ws.pq, last ? (float*)a.ws.gq : (float*)nullptr,
-                                   lb_grad_nsplit_t(a), 1, 1, ks, 0);
+                launch_finish(a, (float*)a.ws.xq, (float*)a.ws.pq, last ? (float*)a.ws.gq : (float*)nullptr,
+                              lb_grad_nsplit_t(a), 1, 1, ks, 0, s);
                 if (last) (void)launch_lr16_logp(a, (const float*)a.ws.xq, s);
                 break;
             }
