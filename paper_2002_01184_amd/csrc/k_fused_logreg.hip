@@ -77,24 +77,6 @@ __device__ __forceinline__ float rows4_scatter(float a0, float a1, float a2, flo
     return __uint_as_float(t[0]) + __uint_as_float(t[1]);
 }
 
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-    const uint64_t u = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xf, 0xf, true);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
-
-// Sum of rows 2k and 2k+1 (k = 0, 1), in both rows.
-__device__ __forceinline__ double rows2_sum(double v) {
-    const uint64_t u = (uint64_t)__double_as_longlong(v);
-    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
-    const double a = __longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0]));
-    const double b = __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1]));
-    return a + b;
-}
-
 // Sum over the 32 lanes of each half wave, as a butterfly: every step adds a
 // lane's value and its partner's, so all 32 lanes end with the same bits.
 __device__ __forceinline__ double half_wave_sum(double v) {
@@ -109,12 +91,7 @@ __device__ __forceinline__ double half_wave_sum(double v) {
 __device__ __forceinline__ double same_j_sum(double v) {
     v += dpp_f64<0x124>(v);   // row_ror 4
     v += dpp_f64<0x128>(v);   // row_ror 8
-    const uint64_t u = (uint64_t)__double_as_longlong(v);
-    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
-    v = __longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0])) +
-        __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1]));
-    return rows2_sum(v);
+    return rows2_sum(xor32_sum(v));
 }
 
 // The logistic link of one row from e = e^-|s| (hardware exp2, about 1 ulp):
