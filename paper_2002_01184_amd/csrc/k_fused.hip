@@ -23,8 +23,20 @@ struct ChainCtl {
     DualAvg da;
 };
 
+// dual_avg_apply with its fused multiply-adds written out (as the compiler
+// contracts it where the factors are computed in place), so that every kernel
+// here rounds alike.
+__device__ __forceinline__ double dual_avg_apply_fma(DualAvg& s, const DaConst& c, double alpha, double delta) {
+    s.hbar = fma(1.0 - c.w, s.hbar, c.w * (delta - alpha));
+    const double log_eps = fma(-c.k, s.hbar, s.mu);
+    s.log_eps_bar = fma(1.0 - c.eta, s.log_eps_bar, c.eta * log_eps);
+    return log_eps;
+}
+
+template <bool OUT, typename DaOf>
 __device__ __forceinline__ void after_decision(const FusedRun& r, int64_t C, int64_t c, int64_t i, bool acc,
-                                               double lar, double dh, double lp_new, ChainCtl& s, bool writer) {
+                                               double lar, double dh, double lp_new, ChainCtl& s, bool writer,
+                                               DaOf da_of) {
     const double eps_used = s.eps;
     if (r.adapt && i < r.n_burnin) {
         const double alpha = lar < 0.0 ? exp(lar) : 1.0;
@@ -32,7 +44,7 @@ __device__ __forceinline__ void after_decision(const FusedRun& r, int64_t C, int
             s.eps = simple_adapt(s.eps, alpha, r.target_accept, r.rate);
         } else {
             const int64_t m = r.m_offset + i + 1;
-            const double log_eps = dual_avg_update(s.da, (double)m, alpha, r.target_accept, r.gamma, r.t0, r.kappa);
+            const double log_eps = dual_avg_apply_fma(s.da, da_of(m), alpha, r.target_accept);
             s.eps = (m < r.adapt_total) ? exp(log_eps) : exp(s.da.log_eps_bar);
         }
     }
@@ -44,6 +56,7 @@ __device__ __forceinline__ void after_decision(const FusedRun& r, int64_t C, int
         if (r.trace.log_accept_ratio) r.trace.log_accept_ratio[k] = lar;
         if (r.trace.target_log_prob) r.trace.target_log_prob[k] = lp_new;
     }
+    if (!OUT) return;
     if (r.out.is_accepted) r.out.is_accepted[c] = acc ? 1 : 0;
     if (r.out.log_accept_ratio) r.out.log_accept_ratio[c] = lar;
     if (r.out.target_log_prob) r.out.target_log_prob[c] = lp_new;
@@ -59,154 +72,181 @@ __device__ __forceinline__ void after_decision(const FusedRun& r, int64_t C, int
 // (slot) s holds replica s % K of chain index s / K; K divides the 64 / G slots
 // of a wavefront, so the two chains of every pair exchange by shuffles G lanes
 // apart.
-template <typename T, int G, int NB, bool EX>
-__device__ __forceinline__ void fused_elem_body(const PlainArgs& a, const FusedRun& r, int64_t lblock) {
-    const int64_t gid = lblock * blockDim.x + threadIdx.x;
-    const int lane = threadIdx.x % G;
-    const int nrep = EX ? r.remc_K : 0;
-    const int64_t slot = gid / G;
-    const int krep = nrep > 1 ? (int)(slot % nrep) : 0;
-    const int64_t c = nrep > 1 ? krep * r.remc_M + slot / nrep : slot;
-    const bool active = slot < a.C;                  // with the exchange: chain index slot / K < M
-    const int64_t cc = active ? c : 0;
-    const int64_t D = a.tg.D;
-    const bool diag = a.tg.kind == HMC_TGT_GAUSS_DIAG;
-    T* X = (T*)a.ws.x;
-    T* Gr = (T*)a.ws.g;
-    const T* prec = (const T*)a.tg.prec;
-
-    // Transformed kernel (x = shift + scale z): the chain runs in z = x / scale,
-    // whose precision is prec scale^2; states are converted at load and store.
-    const double* sc = EX ? a.ws.scale : nullptr;
-    const bool trs = sc != nullptr;
-    // the scale in the state's precision, staged once in LDS for the stores
-    // of x (a lane group covers 4 G NB >= D dims)
-    __shared__ T sc_lds[EX ? 4 * G * NB : 1];
-    if (EX) {
-        if (trs)
-            for (int64_t d = threadIdx.x; d < D; d += blockDim.x) sc_lds[d] = (T)sc[d];
-        __syncthreads();
-    }
-    T x[NB][4], g[NB][4], pr[NB][4];
-    bool ok[NB][4];
-#pragma unroll
-    for (int k = 0; k < NB; ++k)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t d = 4 * (lane + (int64_t)G * k) + j;
-            ok[k][j] = active && d < D;
-            x[k][j] = ok[k][j] ? X[cc * D + d] : (T)0;
-            g[k][j] = ok[k][j] ? Gr[cc * D + d] : (T)0;
-            pr[k][j] = ok[k][j] ? (diag ? prec[d] : (T)1) : (T)0;
-            if (sc && ok[k][j]) {
-                const double sd = sc[d];
-                pr[k][j] = (T)((double)pr[k][j] * sd * sd);
-                x[k][j] = (T)((double)x[k][j] / sd);
-                g[k][j] = (T)((double)g[k][j] * sd);
-            }
-        }
+// Transformed kernel (x = shift + scale z, EX): the chain runs in z = x / scale,
+// whose precision is prec scale^2; states are converted at load and store.
+// ND: dims of a block held (4, or the dims themselves where they are fewer).
+template <typename T, int G, int NB, bool EX, int ND = 4>
+struct ElemChain {
+    T x[NB][ND], g[NB][ND], pr[NB][ND];
+    bool ok[NB][ND];
     ChainCtl s;
-    s.logp = a.ws.logp[cc];
-    s.eps = a.ws.eps[cc];
-    s.da = a.ws.da[cc];
-    const double bt = a.ws.beta ? a.ws.beta[cc] : 1.0;   // inverse temperature of the chain
+    double bt;               // inverse temperature of the chain
+    int lane, nrep, krep;
+    int64_t c, cc;
+    bool active;
+    const double* sc;        // the transform's scale, or NULL
+    const T* sc_lds;         // and in the state's precision, staged in LDS for the stores of x
 
-    for (int64_t i = 0; i < r.n_transitions; ++i) {
-        const uint32_t t = (uint32_t)(r.t_begin + i);
+    // slot: the lane group's index over the whole launch
+    __device__ __forceinline__ void load(const PlainArgs& a, const FusedRun& r, int64_t slot, int lane_,
+                                         const T* sc_lds_) {
+        lane = lane_;
+        nrep = EX ? r.remc_K : 0;
+        krep = nrep > 1 ? (int)(slot % nrep) : 0;
+        c = nrep > 1 ? krep * r.remc_M + slot / nrep : slot;
+        active = slot < a.C;                  // with the exchange: chain index slot / K < M
+        cc = active ? c : 0;
+        sc = EX ? a.ws.scale : nullptr;
+        sc_lds = sc_lds_;
+        const int64_t D = a.tg.D;
+        const bool diag = a.tg.kind == HMC_TGT_GAUSS_DIAG;
+        const T* X = (const T*)a.ws.x;
+        const T* Gr = (const T*)a.ws.g;
+        const T* prec = (const T*)a.tg.prec;
+#pragma unroll
+        for (int k = 0; k < NB; ++k)
+#pragma unroll
+            for (int j = 0; j < ND; ++j) {
+                const int64_t d = 4 * (lane + (int64_t)G * k) + j;
+                ok[k][j] = active && d < D;
+                x[k][j] = ok[k][j] ? X[cc * D + d] : (T)0;
+                g[k][j] = ok[k][j] ? Gr[cc * D + d] : (T)0;
+                pr[k][j] = ok[k][j] ? (diag ? prec[d] : (T)1) : (T)0;
+                if (sc && ok[k][j]) {
+                    const double sd = sc[d];
+                    pr[k][j] = (T)((double)pr[k][j] * sd * sd);
+                    x[k][j] = (T)((double)x[k][j] / sd);
+                    g[k][j] = (T)((double)g[k][j] * sd);
+                }
+            }
+        s.logp = a.ws.logp[cc];
+        s.eps = a.ws.eps[cc];
+        s.da = a.ws.da[cc];
+        bt = a.ws.beta ? a.ws.beta[cc] : 1.0;
+    }
+
+    // Transition i of the launch, t of the run.  Random numbers and the
+    // dual-averaging factors through draw(k, z) (momenta of block k), log_u(),
+    // log_swap(ca) (exchange uniform of the pair whose first chain is ca) and
+    // da_of(m), so that they can be computed here or taken from LDS.
+    // OUT: the outputs of hmc_step may be asked for (single transitions).
+    template <bool OUT, typename Draw, typename LogU, typename LogSwap, typename DaOf>
+    __device__ __forceinline__ void transition(const PlainArgs& a, const FusedRun& r, int64_t i, uint32_t t, Draw draw,
+                                               LogU log_u, LogSwap log_swap, DaOf da_of) {
+        const int64_t D = a.tg.D;
+        const bool trs = sc != nullptr;
         const T eps = (T)s.eps;                   // drift
         const T half = (T)(0.5 * s.eps * bt);     // kicks: beta eps (replica exchange; beta = 1 otherwise)
         const T keps = (T)(s.eps * bt);
-        T xn[NB][4], pn[NB][4], gn[NB][4];
+        T xn[NB][ND], pn[NB][ND], gn[NB][ND];
+        // dk and lp are summed without their factor 1/2 (exact in binary, applied below)
         double dk = 0.0;
 #pragma unroll
         for (int k = 0; k < NB; ++k) {
             T z[4];
-            momentum4<T>(a.key, (uint32_t)cc, t, (uint32_t)(lane + G * k), z,
-                         4 * (lane + (int64_t)G * k) + 2 < D);
+            draw(k, z);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
+            for (int j = 0; j < ND; ++j) {
                 const T p0 = ok[k][j] ? z[j] : (T)0;
-                dk -= 0.5 * (double)p0 * (double)p0;
+                dk = fma(-(double)p0, (double)p0, dk);
                 xn[k][j] = x[k][j];
                 pn[k][j] = fma(half, g[k][j], p0);
             }
         }
-        for (int l = 0; l < a.L; ++l) {
-            const T ke = (l == a.L - 1) ? half : keps;
+        auto leap = [&](T ke) {
 #pragma unroll
             for (int k = 0; k < NB; ++k)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
+                for (int j = 0; j < ND; ++j) {
                     xn[k][j] = fma(eps, pn[k][j], xn[k][j]);
                     gn[k][j] = -pr[k][j] * xn[k][j];
                     pn[k][j] = fma(ke, gn[k][j], pn[k][j]);
                 }
+        };
+        // The last step apart: in FP64 the choice of the factor in the chain of
+        // dependent operations is not free (D = 1 run 158 -> 154 us, D = 37 135 ->
+        // 128); in FP32 the shorter code is (D = 1000, 1000 chains 907 against 934).
+        if constexpr (sizeof(T) == 8) {
+            for (int l = 1; l < a.L; ++l) leap(keps);
+            leap(half);
+        } else {
+            for (int l = 0; l < a.L; ++l) leap(l == a.L - 1 ? half : keps);
         }
         double lp = 0.0;
 #pragma unroll
         for (int k = 0; k < NB; ++k)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                dk += 0.5 * (double)pn[k][j] * (double)pn[k][j];
-                lp += 0.5 * (double)xn[k][j] * (double)gn[k][j];
+            for (int j = 0; j < ND; ++j) {
+                dk = fma((double)pn[k][j], (double)pn[k][j], dk);
+                lp = fma((double)xn[k][j], (double)gn[k][j], lp);
             }
-        dk = group_sum<G>(dk);
-        lp = group_sum<G>(lp);
+        dk = 0.5 * group_sum<G>(dk);
+        lp = 0.5 * group_sum<G>(lp);
         const double dh = -(bt * lp) + bt * s.logp + dk;
         const double lar = log_accept_ratio_of(dh);
-        const bool acc = log_accept_uniform(a.key, (uint32_t)cc, t) < lar;
+        const bool acc = log_u() < lar;
         if (acc) {
 #pragma unroll
             for (int k = 0; k < NB; ++k)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
+                for (int j = 0; j < ND; ++j) {
                     x[k][j] = xn[k][j];
                     g[k][j] = gn[k][j];
                 }
             s.logp = lp;
         }
+        // four dims of a row at p + d, as one store where the block is whole (rows are
+        // at least element-aligned)
+        struct __attribute__((packed, aligned(sizeof(T)))) T4 { T v[ND]; };
+        auto store4 = [&](T* p, int k, const T (&v)[ND]) {
+            if (ok[k][ND - 1]) {
+                T4 o;
+#pragma unroll
+                for (int j = 0; j < ND; ++j) o.v[j] = v[j];
+                *(T4*)p = o;
+            } else {
+#pragma unroll
+                for (int j = 0; j < ND - 1; ++j)
+                    if (ok[k][j]) p[j] = v[j];
+            }
+        };
         // kept sample and proposal outputs of this transition
         auto store_outputs = [&]() {
+            int l4 = 4 * lane;
+            // an index the compiler cannot see through keeps the LDS reads of the scale
+            // here: hoisted out of the transition loop they would hold NB 4 registers
+            // for the whole run
+            if (EX) asm volatile("" : "+v"(l4));
+            auto scaled = [&](int k, const T (&v)[ND], T (&o)[ND]) {
+#pragma unroll
+                for (int j = 0; j < ND; ++j) o[j] = (EX && trs) ? v[j] * sc_lds[l4 + 4 * G * k + j] : v[j];
+            };
             if (r.samples && i >= r.n_burnin) {
                 T* smp = (T*)r.samples + ((i - r.n_burnin) * a.C + c) * D;
-                if (EX && trs) {
-                    // an index the compiler cannot see through keeps the LDS
-                    // reads here: hoisted out of the transition loop they
-                    // would hold NB 4 registers for the whole run
-                    int l4 = 4 * lane;
-                    asm volatile("" : "+v"(l4));
 #pragma unroll
-                    for (int k = 0; k < NB; ++k)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            if (ok[k][j]) smp[4 * (lane + (int64_t)G * k) + j] = x[k][j] * sc_lds[l4 + 4 * G * k + j];
-                } else {
-#pragma unroll
-                    for (int k = 0; k < NB; ++k)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            if (ok[k][j]) smp[4 * (lane + (int64_t)G * k) + j] = x[k][j];
+                for (int k = 0; k < NB; ++k) {
+                    T o[ND];
+                    scaled(k, x[k], o);
+                    store4(smp + 4 * (lane + (int64_t)G * k), k, o);
                 }
             }
-            if (r.out.proposed_state || r.out.proposed_momentum) {
-                int l4 = 4 * lane;
-                if (EX) asm volatile("" : "+v"(l4));
+            if (OUT && (r.out.proposed_state || r.out.proposed_momentum)) {
 #pragma unroll
-                for (int k = 0; k < NB; ++k)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (ok[k][j]) {
-                            const int64_t d = 4 * (lane + (int64_t)G * k) + j;
-                            if (r.out.proposed_state)
-                                ((T*)r.out.proposed_state)[c * D + d] = (EX && trs) ? xn[k][j] * sc_lds[l4 + 4 * G * k + j] : xn[k][j];
-                            if (r.out.proposed_momentum) ((T*)r.out.proposed_momentum)[c * D + d] = pn[k][j];
-                        }
+                for (int k = 0; k < NB; ++k) {
+                    const int64_t d = c * D + 4 * (lane + (int64_t)G * k);
+                    if (r.out.proposed_state) {
+                        T o[ND];
+                        scaled(k, xn[k], o);
+                        store4((T*)r.out.proposed_state + d, k, o);
+                    }
+                    if (r.out.proposed_momentum) store4((T*)r.out.proposed_momentum + d, k, pn[k]);
+                }
             }
         };
         if (EX) {
             // traces and adaptation record the transition; the exchange follows
             // it, and the kept sample is the state after the exchange
-            if (active) after_decision(r, a.C, c, i, acc, lar, dh, s.logp, s, lane == 0);
+            if (active) after_decision<OUT>(r, a.C, c, i, acc, lar, dh, s.logp, s, lane == 0, da_of);
             if (nrep > 1) {
                 const int par = (int)(t & 1u);
                 const bool a_side = krep >= par && ((krep - par) & 1) == 0 && krep + 1 < nrep;
@@ -217,15 +257,14 @@ __device__ __forceinline__ void fused_elem_body(const PlainArgs& a, const FusedR
                 const double bt_o = __shfl(bt, src, 64);
                 bool swp = false;
                 if (active && (a_side || b_side)) {
-                    const int64_t ca = a_side ? c : c - r.remc_M;
                     const double la = a_side ? s.logp : lp_o, lb = a_side ? lp_o : s.logp;
                     const double ba = a_side ? bt : bt_o, bb = a_side ? bt_o : bt;
-                    swp = log_uniform52(a.key, (uint32_t)ca, t, TAG_SWAP) < (ba - bb) * (lb - la);
+                    swp = log_swap(b_side) < (ba - bb) * (lb - la);
                 }
 #pragma unroll
                 for (int k = 0; k < NB; ++k)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
+                    for (int j = 0; j < ND; ++j) {
                         const T xo = __shfl(x[k][j], src, 64), go = __shfl(g[k][j], src, 64);
                         if (swp) {
                             x[k][j] = xo;
@@ -239,27 +278,224 @@ __device__ __forceinline__ void fused_elem_body(const PlainArgs& a, const FusedR
             if (active) store_outputs();
         } else if (active) {
             store_outputs();
-            after_decision(r, a.C, c, i, acc, lar, dh, s.logp, s, lane == 0);
+            after_decision<OUT>(r, a.C, c, i, acc, lar, dh, s.logp, s, lane == 0, da_of);
         }
     }
-    if (!active) return;
-    // a fresh read of the scale: reusing the values loaded before the loop
-    // would hold them in registers for the whole run
-    if (EX) asm volatile("" ::: "memory");
+
+    __device__ __forceinline__ void store(const PlainArgs& a) {
+        if (!active) return;
+        const int64_t D = a.tg.D;
+        const bool trs = sc != nullptr;
+        T* X = (T*)a.ws.x;
+        T* Gr = (T*)a.ws.g;
+        // a fresh read of the scale: reusing the values loaded before the loop
+        // would hold them in registers for the whole run
+        if (EX) asm volatile("" ::: "memory");
 #pragma unroll
-    for (int k = 0; k < NB; ++k)
+        for (int k = 0; k < NB; ++k)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (ok[k][j]) {
-                const int64_t d = 4 * (lane + (int64_t)G * k) + j;
-                X[c * D + d] = (EX && trs) ? (T)((double)x[k][j] * sc[d]) : x[k][j];
-                Gr[c * D + d] = (EX && trs) ? (T)((double)g[k][j] / sc[d]) : g[k][j];
-            }
-    if (lane == 0) {
-        a.ws.logp[c] = s.logp;
-        a.ws.eps[c] = s.eps;
-        a.ws.da[c] = s.da;
+            for (int j = 0; j < ND; ++j)
+                if (ok[k][j]) {
+                    const int64_t d = 4 * (lane + (int64_t)G * k) + j;
+                    X[c * D + d] = (EX && trs) ? (T)((double)x[k][j] * sc[d]) : x[k][j];
+                    Gr[c * D + d] = (EX && trs) ? (T)((double)g[k][j] / sc[d]) : g[k][j];
+                }
+        if (lane == 0) {
+            a.ws.logp[c] = s.logp;
+            a.ws.eps[c] = s.eps;
+            a.ws.da[c] = s.da;
+        }
     }
+};
+
+// the scale in the state's precision, staged once in LDS for the stores of x (a
+// lane group covers 4 G NB >= D dims)
+template <typename T, bool EX>
+__device__ __forceinline__ void elem_stage_scale(const PlainArgs& a, T* sc_lds) {
+    if (!EX) return;
+    if (a.ws.scale)
+        for (int64_t d = threadIdx.x; d < a.tg.D; d += blockDim.x) sc_lds[d] = (T)a.ws.scale[d];
+    __syncthreads();
+}
+
+template <typename T, int G, int NB, bool EX>
+__device__ __forceinline__ void fused_elem_body(const PlainArgs& a, const FusedRun& r, int64_t lblock) {
+    const int64_t gid = lblock * blockDim.x + threadIdx.x;
+    __shared__ T sc_lds[EX ? 4 * G * NB : 1];
+    elem_stage_scale<T, EX>(a, sc_lds);
+    ElemChain<T, G, NB, EX> ch;
+    ch.load(a, r, gid / G, (int)(threadIdx.x % G), sc_lds);
+    const int64_t D = a.tg.D;
+    for (int64_t i = 0; i < r.n_transitions; ++i) {
+        const uint32_t t = (uint32_t)(r.t_begin + i);
+        ch.template transition<true>(
+            a, r, i, t,
+            [&](int k, T (&z)[4]) {
+                momentum4<T>(a.key, (uint32_t)ch.cc, t, (uint32_t)(ch.lane + G * k), z,
+                             4 * (ch.lane + (int64_t)G * k) + 2 < D);
+            },
+            [&]() { return log_accept_uniform(a.key, (uint32_t)ch.cc, t); },
+            [&](bool b_side) {
+                return log_uniform52(a.key, (uint32_t)(b_side ? ch.c - r.remc_M : ch.c), t, TAG_SWAP);
+            },
+            [&](int64_t m) { return dual_avg_const((double)m, r.gamma, r.t0, r.kappa); });
+    }
+    ch.store(a);
+}
+
+// ---------------------------------------------------------------------------
+// Few chains: when the lane groups of all chains are at most a wavefront per
+// SIMD, a run's time is one wavefront's instruction stream, and two thirds of it
+// are draws (Philox, FP64 logarithms, Box-Muller) that do not depend on the
+// chain.  Here a workgroup of 8 waves owns `chains` chains, as few as spread all
+// of them over the 256 CUs; its first waves run the transitions with momenta,
+// accept and exchange uniforms and dual-averaging factors read from LDS, while
+// the others draw those of the next block of transitions, every lane a different
+// (transition, chain, block).  The arithmetic is that of fused_elem_body on the
+// same numbers: results are bitwise the same.  Whole runs, before and after: N(0,
+// 1) FP64, 100 chains, 400 transitions 485 -> 154 us; diagonal D = 37 FP64, 332
+// chains in 4 replicas, 100 transitions 311 -> 128; D = 333 FP32, 1000 chains, 64
+// transitions 178 -> 115 (there the draws bound it on either side); N(0, I) D = 3
+// FP64, 16384 chains, 80 transitions 159 -> 68.
+// ---------------------------------------------------------------------------
+constexpr int EF_THREADS = 512;
+struct ElemFew {
+    int32_t chains;          // per workgroup
+    int32_t bt;              // transitions per block of draws
+};
+// LDS doubles per chain and transition besides the momenta: accept and exchange uniform; three more per transition
+template <typename T, int G, int NB>
+constexpr size_t elem_few_lds(int chains, int bt) {
+    return (size_t)2 * bt * ((size_t)chains * G * NB * 4 * sizeof(T) + (2 * chains + 4) * sizeof(double));
+}
+
+template <typename T, int G, int NB, bool EX, int ND>
+__global__ __launch_bounds__(EF_THREADS) void k_fused_elem_few(PlainArgs a, FusedRun r, ElemFew f) {
+    extern __shared__ __align__(16) uint8_t few_lds[];
+    __shared__ T sc_lds[EX ? 4 * G * NB : 1];
+    elem_stage_scale<T, EX>(a, sc_lds);
+    struct __attribute__((aligned(16))) Z4 { T v[4]; };
+    const int lw = f.chains * G;                            // owner lanes (<= 256)
+    const int nw = (lw + 63) & ~63;                         // owner threads, whole waves
+    Z4* zb = (Z4*)few_lds;                                  // [2][bt][NB][lw]
+    double* lub = (double*)(zb + (size_t)2 * f.bt * NB * lw);       // [2][bt][chains] log accept uniforms
+    double* swb = lub + (size_t)2 * f.bt * f.chains;        // [2][bt][chains] log exchange uniforms
+    double* dab = swb + (size_t)2 * f.bt * f.chains;        // [2][bt][4] dual-averaging factors
+    const int64_t D = a.tg.D, T0 = r.n_transitions;
+    const int64_t slot0 = (int64_t)blockIdx.x * f.chains;
+    const int nrep = EX ? r.remc_K : 0;
+    auto chain_of = [&](int s) -> int64_t {
+        const int64_t slot = slot0 + s;
+        if (slot >= a.C) return -1;
+        return nrep > 1 ? (slot % nrep) * r.remc_M + slot / nrep : slot;
+    };
+    // A thread's tasks of a block of draws: me, me + n, ... as (transition q, chain
+    // cs, part p of np), stepped without divisions.
+    struct Task {
+        int q, cs, p, dq, dcs, dp, np, nc;
+        __device__ __forceinline__ void init(int me, int n, int np_, int nc_) {
+            np = np_;
+            nc = nc_;
+            p = me % np; cs = me / np % nc; q = me / np / nc;
+            dp = n % np; dcs = n / np % nc; dq = n / np / nc;
+        }
+        __device__ __forceinline__ void next() {
+            p += dp;
+            const int c1 = p >= np ? 1 : 0;
+            p -= c1 ? np : 0;
+            cs += dcs + c1;
+            const int c2 = cs >= nc ? 1 : 0;
+            cs -= c2 ? nc : 0;
+            q += dq + c2;
+        }
+    };
+    const int nblk = (int)((D + 3) / 4);
+    // draws of transitions i0 .. i0 + bt - 1 into half b, by threads me of n: one block
+    // of four dims per task, and the uniforms by threads of their own (zt counts from
+    // the first thread, ut from the last)
+    auto produce = [&](int64_t i0, int b, Task zt, Task ut, int mine, int n) {
+        const int nt = T0 - i0 < f.bt ? (int)(T0 - i0) : f.bt;
+        for (; zt.q < nt; zt.next()) {
+            const int64_t c = chain_of(zt.cs);
+            if (c >= 0) {
+                Z4 z;
+                momentum4<T>(a.key, (uint32_t)c, (uint32_t)(r.t_begin + i0 + zt.q), (uint32_t)zt.p, z.v,
+                             4 * (int64_t)zt.p + 2 < D);
+                zb[((size_t)b * f.bt + zt.q) * (NB * lw) + (zt.p / G) * lw + zt.cs * G + zt.p % G] = z;
+            }
+        }
+        for (; ut.q < nt; ut.next()) {
+            const int64_t c = chain_of(ut.cs);
+            if (c < 0) continue;
+            const uint32_t t = (uint32_t)(r.t_begin + i0 + ut.q);
+            lub[((size_t)b * f.bt + ut.q) * f.chains + ut.cs] = log_accept_uniform(a.key, (uint32_t)c, t);
+            if (EX && nrep > 1)
+                swb[((size_t)b * f.bt + ut.q) * f.chains + ut.cs] = log_uniform52(a.key, (uint32_t)c, t, TAG_SWAP);
+        }
+        if (r.adapt && r.adapt_kind != HMC_ADAPT_SIMPLE)
+            for (int q = mine; q < nt; q += n)
+                if (i0 + q < r.n_burnin) {
+                    const DaConst o = dual_avg_const((double)(r.m_offset + i0 + q + 1), r.gamma, r.t0, r.kappa);
+                    double* d = dab + ((size_t)b * f.bt + q) * 4;
+                    d[0] = o.w;
+                    d[1] = o.k;
+                    d[2] = o.eta;
+                }
+    };
+    const int tid = (int)threadIdx.x;
+    const bool owner = tid < lw;
+    ElemChain<T, G, NB, EX, ND> ch;
+    if (owner) ch.load(a, r, slot0 + tid / G, tid % G, sc_lds);
+    {
+        Task zt, ut;
+        zt.init(tid, EF_THREADS, nblk, f.chains);
+        ut.init(EF_THREADS - 1 - tid, EF_THREADS, 1, f.chains);
+        produce(0, 0, zt, ut, EF_THREADS - 1 - tid, EF_THREADS);
+    }
+    Task zt, ut;
+    const int np = EF_THREADS - nw, me = tid >= nw ? tid - nw : 0;
+    zt.init(me, np, nblk, f.chains);
+    ut.init(np - 1 - me, np, 1, f.chains);
+    __syncthreads();
+    int b = 0;
+    for (int64_t i0 = 0; i0 < T0; i0 += f.bt, b ^= 1) {
+        if (tid >= nw) {
+            if (i0 + f.bt < T0) produce(i0 + f.bt, b ^ 1, zt, ut, np - 1 - me, np);
+        } else if (owner) {
+            const int nt = T0 - i0 < f.bt ? (int)(T0 - i0) : f.bt;
+            const Z4* zq = zb + (size_t)b * f.bt * (NB * lw) + tid;
+            const double* lq = lub + (size_t)b * f.bt * f.chains + tid / G;
+            const double* sq = swb + (size_t)b * f.bt * f.chains + tid / G;
+            const double* dq = dab + (size_t)b * f.bt * 4;
+            // the draws of a transition are read during the one before it
+            Z4 zc[NB];
+#pragma unroll
+            for (int k = 0; k < NB; ++k) zc[k] = zq[k * lw];
+            double lc = *lq;
+            for (int q = 0; q < nt; ++q) {
+                const int more = q + 1 < nt ? 1 : 0;
+                zq += more * (NB * lw);
+                lq += more * f.chains;
+                Z4 zn[NB];
+#pragma unroll
+                for (int k = 0; k < NB; ++k) zn[k] = zq[k * lw];
+                const double ln = *lq;
+                ch.template transition<false>(
+                    a, r, i0 + q, (uint32_t)(r.t_begin + i0 + q),
+                    [&](int k, T (&z)[4]) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) z[j] = zc[k].v[j];
+                    },
+                    [&]() { return lc; }, [&](bool b_side) { return sq[q * f.chains - (b_side ? 1 : 0)]; },
+                    [&](int64_t) { return DaConst{dq[4 * q], dq[4 * q + 1], dq[4 * q + 2]}; });
+#pragma unroll
+                for (int k = 0; k < NB; ++k) zc[k] = zn[k];
+                lc = ln;
+            }
+        }
+        __syncthreads();
+    }
+    if (owner) ch.store(a);
 }
 
 template <typename T, int G, int NB, bool EX>
@@ -481,7 +717,10 @@ __global__ __launch_bounds__(64 * DENSE_NW) void k_fused_dense(PlainArgs a, Fuse
         }
         // traces and adaptation record the transition; the exchange follows it,
         // and the kept sample is the state after the exchange
-        if (cvalid) after_decision(r, a.C, c, i, acc, lar, dh, s.logp, s, w == 0 && g4 == 0);
+        if (cvalid)
+            after_decision<true>(r, a.C, c, i, acc, lar, dh, s.logp, s, w == 0 && g4 == 0, [&](int64_t m) {
+                return dual_avg_const((double)m, r.gamma, r.t0, r.kappa);
+            });
         if (EX && nrep > 1) {
             const int par = (int)(t & 1u);
             const bool a_side = krep >= par && ((krep - par) & 1) == 0 && krep + 1 < nrep;
@@ -636,11 +875,57 @@ bool fused_remc_inline(const PlainArgs& a, int64_t K) {
     default: MACRO(64, 8); break;                      \
     }
 
+// The few-chain kernel: the lanes of all chains fill at most one wavefront per
+// SIMD (1024; beyond, two of fused_elem_body's wavefronts hide each other's
+// waits), and the owners' state fits the registers of 8 waves per CU.
+template <typename T, int G, int NB>
+static bool launch_elem_few(const PlainArgs& a, const FusedRun& r, hipStream_t s) {
+    if constexpr (NB * sizeof(T) > 16) {
+        return false;
+    } else {
+        if (a.C * G > 65536 || r.n_transitions < 2) return false;
+        const int64_t unit = r.remc_K > 1 ? r.remc_K : 1;              // a pair's chains share a wavefront
+        int64_t chains = (a.C + 255) / 256;
+        chains = (chains + unit - 1) / unit * unit;
+        if (chains * G > 256) return false;
+        if (unit > 1 && (64 / G) % unit != 0) return false;
+        ElemFew f;
+        f.chains = (int32_t)chains;
+        const int64_t zbytes = chains * G * NB * 4 * (int64_t)sizeof(T);
+        int64_t bt = 32768 / zbytes;
+        f.bt = (int32_t)(bt > 64 ? 64 : (bt < 1 ? 1 : bt));
+        const size_t lds = elem_few_lds<T, G, NB>(f.chains, f.bt);
+        const dim3 grid((unsigned)((a.C + chains - 1) / chains));
+        if (r.out.is_accepted || r.out.log_accept_ratio || r.out.target_log_prob || r.out.delta_h ||
+            r.out.proposed_state || r.out.proposed_momentum)
+            return false;
+        auto go = [&](auto kern) {
+            if (lds > 65536)
+                (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            hipLaunchKernelGGL(kern, grid, dim3(EF_THREADS), lds, s, a, r, f);
+        };
+        const bool ex = a.ws.scale || r.remc_K > 1;
+        if constexpr (G == 1) {
+            if (a.tg.D <= 2) {
+                if (a.tg.D == 1) ex ? go(k_fused_elem_few<T, 1, 1, true, 1>) : go(k_fused_elem_few<T, 1, 1, false, 1>);
+                else ex ? go(k_fused_elem_few<T, 1, 1, true, 2>) : go(k_fused_elem_few<T, 1, 1, false, 2>);
+                return true;
+            }
+        }
+        if (ex) go(k_fused_elem_few<T, G, NB, true, 4>);
+        else go(k_fused_elem_few<T, G, NB, false, 4>);
+        return true;
+    }
+}
+
 template <typename T>
 static hipError_t launch_elem(const PlainArgs& a, const FusedRun& r, hipStream_t s) {
     const int cls = elem_class(a);
     const dim3 grid((unsigned)elem_blocks(a));
     if (r.remc_K > 1 && !fused_remc_inline(a, r.remc_K)) return hipErrorInvalidValue;
+#define HMC_ELEM_FEW(GG, NN) if (launch_elem_few<T, GG, NN>(a, r, s)) return hipGetLastError()
+    HMC_ELEM_DISPATCH(cls, HMC_ELEM_FEW)
+#undef HMC_ELEM_FEW
     if (a.ws.scale || r.remc_K > 1) {
 #define HMC_ELEM(GG, NN) hipLaunchKernelGGL((k_fused_elem<T, GG, NN, true>), grid, dim3(256), 0, s, a, r)
         HMC_ELEM_DISPATCH(cls, HMC_ELEM)
