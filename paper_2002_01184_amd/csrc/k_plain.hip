@@ -1279,40 +1279,68 @@ hipError_t launch_da_init(const PlainArgs& a, hipStream_t s) {
 // Streaming expectations: element e = (c, d) of q kept states in draw order.
 // Welford (1962): n-th draw of a half, delta = x - mean, mean += delta / n,
 // m2 += delta (x - mean); batch sums accumulate in a register and are added
-// to memory when the batch changes (a batch may span chunks).
+// to memory when the batch changes (a batch may span chunks).  Bound by the
+// ring's bytes where the divisions are not: delta / n is formed from the
+// correctly rounded reciprocal of n, once per draw, by a multiplication and one
+// correction step, which gives the correctly rounded quotient (Markstein 1990)
+// wherever the quotient's own corrections are normal numbers, and by a division
+// elsewhere; eight draws are loaded ahead of their use.  64 draws of 1000 x 333
+// FP32 (85 MB): 43 -> 30 us.
+__device__ __forceinline__ double div_by_count(double delta, double n, double rn) {
+    const double q = delta * rn;
+    const double a = fabs(q);
+    if (!(a > 0x1p-900 && a < 0x1p900)) return delta / n;      // zero, tiny, huge or not finite
+    return fma(fma(-n, q, delta), rn, q);
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void k_moments(const T* __restrict__ ring, int64_t n_el, int64_t q, int64_t r0,
                                                  int64_t R, double* __restrict__ mean, double* __restrict__ m2,
                                                  double* __restrict__ bsum, int64_t blen) {
     const int64_t half = R / 2;
+    auto count = [&](int64_t j) {                  // the draw's number within its half
+        const int64_t r = r0 + j;
+        return (double)(r < half ? r + 1 : r - half + 1);
+    };
+    constexpr int NR = 256;
+    __shared__ double rcp[NR];                     // 1 / count of the first draws
+    if ((int64_t)threadIdx.x < q) rcp[threadIdx.x] = 1.0 / count(threadIdx.x);
+    __syncthreads();
+    const int64_t split = half - r0 < 0 ? 0 : (half - r0 < q ? half - r0 : q);   // draws 0 .. split - 1 are in half 0
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n_el; e += (int64_t)gridDim.x * blockDim.x) {
-        double mu[2] = {mean[e], mean[n_el + e]};
-        double ss[2] = {m2[e], m2[n_el + e]};
-        int64_t cur_b = -1;
+        int64_t cur_b = bsum ? r0 / blen : 0, next_b = bsum ? (cur_b + 1) * blen : 0;
         double bacc = 0.0;
-        for (int64_t j = 0; j < q; ++j) {
-            const int64_t r = r0 + j;
-            const double x = (double)ring[j * n_el + e];
-            const int h = r < half ? 0 : 1;
-            const double n = (double)(h ? r - half + 1 : r + 1);
-            const double delta = x - mu[h];
-            mu[h] += delta / n;
-            ss[h] += delta * (x - mu[h]);
-            if (bsum) {
-                const int64_t b = r / blen;
-                if (b != cur_b) {
-                    if (cur_b >= 0) bsum[cur_b * n_el + e] += bacc;
-                    cur_b = b;
-                    bacc = 0.0;
+        for (int h = 0; h < 2; ++h) {
+            const int64_t j0 = h ? split : 0, j1 = h ? q : split;
+            if (j0 >= j1) continue;
+            double mu = mean[h * n_el + e], ss = m2[h * n_el + e];
+            auto draw = [&](int64_t j, T v) {
+                const double x = (double)v, n = count(j), delta = x - mu;
+                mu += div_by_count(delta, n, j < NR ? rcp[j] : 1.0 / n);
+                ss += delta * (x - mu);
+                if (bsum) {
+                    if (r0 + j == next_b) {
+                        bsum[cur_b * n_el + e] += bacc;
+                        ++cur_b;
+                        next_b += blen;
+                        bacc = 0.0;
+                    }
+                    bacc += x;
                 }
-                bacc += x;
+            };
+            int64_t j = j0;
+            for (; j + 8 <= j1; j += 8) {
+                T v[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = ring[(j + k) * n_el + e];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) draw(j + k, v[k]);
             }
+            for (; j < j1; ++j) draw(j, ring[j * n_el + e]);
+            mean[h * n_el + e] = mu;
+            m2[h * n_el + e] = ss;
         }
-        if (bsum && cur_b >= 0) bsum[cur_b * n_el + e] += bacc;
-        mean[e] = mu[0];
-        mean[n_el + e] = mu[1];
-        m2[e] = ss[0];
-        m2[n_el + e] = ss[1];
+        if (bsum) bsum[cur_b * n_el + e] += bacc;
     }
 }
 
