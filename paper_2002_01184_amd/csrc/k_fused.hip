@@ -126,13 +126,14 @@ struct ElemChain {
     }
 
     // Transition i of the launch, t of the run.  Random numbers and the
-    // dual-averaging factors through draw(k, z) (momenta of block k), log_u(),
-    // log_swap(ca) (exchange uniform of the pair whose first chain is ca) and
-    // da_of(m), so that they can be computed here or taken from LDS.
+    // dual-averaging factors through draw(k, z) (momenta of block k), accept(lar)
+    // (log of the accept uniform < lar), swap(b_side, thr) (log of the exchange
+    // uniform of this chain's pair < thr) and da_of(m), so that they can be computed
+    // here or taken from LDS.
     // OUT: the outputs of hmc_step may be asked for (single transitions).
-    template <bool OUT, typename Draw, typename LogU, typename LogSwap, typename DaOf>
+    template <bool OUT, typename Draw, typename Accept, typename Swap, typename DaOf>
     __device__ __forceinline__ void transition(const PlainArgs& a, const FusedRun& r, int64_t i, uint32_t t, Draw draw,
-                                               LogU log_u, LogSwap log_swap, DaOf da_of) {
+                                               Accept accept, Swap swap, DaOf da_of) {
         const int64_t D = a.tg.D;
         const bool trs = sc != nullptr;
         const T eps = (T)s.eps;                   // drift
@@ -184,7 +185,7 @@ struct ElemChain {
         lp = 0.5 * group_sum<G>(lp);
         const double dh = -(bt * lp) + bt * s.logp + dk;
         const double lar = log_accept_ratio_of(dh);
-        const bool acc = log_u() < lar;
+        const bool acc = accept(lar);
         if (acc) {
 #pragma unroll
             for (int k = 0; k < NB; ++k)
@@ -259,7 +260,7 @@ struct ElemChain {
                 if (active && (a_side || b_side)) {
                     const double la = a_side ? s.logp : lp_o, lb = a_side ? lp_o : s.logp;
                     const double ba = a_side ? bt : bt_o, bb = a_side ? bt_o : bt;
-                    swp = log_swap(b_side) < (ba - bb) * (lb - la);
+                    swp = swap(b_side, (ba - bb) * (lb - la));
                 }
 #pragma unroll
                 for (int k = 0; k < NB; ++k)
@@ -334,9 +335,9 @@ __device__ __forceinline__ void fused_elem_body(const PlainArgs& a, const FusedR
                 momentum4<T>(a.key, (uint32_t)ch.cc, t, (uint32_t)(ch.lane + G * k), z,
                              4 * (ch.lane + (int64_t)G * k) + 2 < D);
             },
-            [&]() { return log_accept_uniform(a.key, (uint32_t)ch.cc, t); },
-            [&](bool b_side) {
-                return log_uniform52(a.key, (uint32_t)(b_side ? ch.c - r.remc_M : ch.c), t, TAG_SWAP);
+            [&](double lar) { return accept_below(a.key, (uint32_t)ch.cc, t, lar); },
+            [&](bool b_side, double thr) {
+                return log_uniform52_below(a.key, (uint32_t)(b_side ? ch.c - r.remc_M : ch.c), t, TAG_SWAP, thr);
             },
             [&](int64_t m) { return dual_avg_const((double)m, r.gamma, r.t0, r.kappa); });
     }
@@ -354,8 +355,8 @@ __device__ __forceinline__ void fused_elem_body(const PlainArgs& a, const FusedR
 // (transition, chain, block).  The arithmetic is that of fused_elem_body on the
 // same numbers: results are bitwise the same.  Whole runs, before and after: N(0,
 // 1) FP64, 100 chains, 400 transitions 485 -> 154 us; diagonal D = 37 FP64, 332
-// chains in 4 replicas, 100 transitions 311 -> 128; D = 333 FP32, 1000 chains, 64
-// transitions 178 -> 115 (there the draws bound it on either side); N(0, I) D = 3
+// chains in 4 replicas, 100 transitions 311 -> 130; D = 333 FP32, 1000 chains, 64
+// transitions 178 -> 103 (there the draws bound it on either side); N(0, I) D = 3
 // FP64, 16384 chains, 80 transitions 159 -> 68.
 // ---------------------------------------------------------------------------
 constexpr int EF_THREADS = 512;
@@ -480,13 +481,15 @@ __global__ __launch_bounds__(EF_THREADS) void k_fused_elem_few(PlainArgs a, Fuse
 #pragma unroll
                 for (int k = 0; k < NB; ++k) zn[k] = zq[k * lw];
                 const double ln = *lq;
+                const double own = EX ? sq[q * f.chains] : 0.0, below = EX ? sq[q * f.chains - 1] : 0.0;
                 ch.template transition<false>(
                     a, r, i0 + q, (uint32_t)(r.t_begin + i0 + q),
                     [&](int k, T (&z)[4]) {
 #pragma unroll
                         for (int j = 0; j < 4; ++j) z[j] = zc[k].v[j];
                     },
-                    [&]() { return lc; }, [&](bool b_side) { return sq[q * f.chains - (b_side ? 1 : 0)]; },
+                    [&](double lar) { return lc < lar; },
+                    [&](bool b_side, double thr) { return (b_side ? below : own) < thr; },
                     [&](int64_t) { return DaConst{dq[4 * q], dq[4 * q + 1], dq[4 * q + 2]}; });
 #pragma unroll
                 for (int k = 0; k < NB; ++k) zc[k] = zn[k];
@@ -704,7 +707,7 @@ __global__ __launch_bounds__(64 * DENSE_NW) void k_fused_dense(PlainArgs a, Fuse
         }
         const double dh = -(bt * lp) + bt * s.logp + dk;
         const double lar = log_accept_ratio_of(dh);
-        const bool acc = log_accept_uniform(a.key, (uint32_t)cc, t) < lar;
+        const bool acc = accept_below(a.key, (uint32_t)cc, t, lar);
         if (acc) {
 #pragma unroll
             for (int m = 0; m < MT; ++m)
@@ -733,7 +736,7 @@ __global__ __launch_bounds__(64 * DENSE_NW) void k_fused_dense(PlainArgs a, Fuse
                 const int64_t ca = a_side ? c : c - r.remc_M;
                 const double la = a_side ? s.logp : lp_o, lb = a_side ? lp_o : s.logp;
                 const double ba = a_side ? bt : bt_o, bb = a_side ? bt_o : bt;
-                swp = log_uniform52(a.key, (uint32_t)ca, t, TAG_SWAP) < (ba - bb) * (lb - la);
+                swp = log_uniform52_below(a.key, (uint32_t)ca, t, TAG_SWAP, (ba - bb) * (lb - la));
             }
 #pragma unroll
             for (int m = 0; m < MT; ++m)

@@ -485,7 +485,7 @@ __global__ __launch_bounds__(512) void k_fused_logreg4(PlainArgs a, FusedRun r) 
                     const int64_t ca = a_side ? oc : pc;
                     const double la = a_side ? lo : lq, lb = a_side ? lq : lo;
                     const double ba = a_side ? btd : bq, bb = a_side ? bq : btd;
-                    swp = log_uniform52(a.key, (uint32_t)ca, tt, TAG_SWAP) < (ba - bb) * (lb - la);
+                    swp = log_uniform52_below(a.key, (uint32_t)ca, tt, TAG_SWAP, (ba - bb) * (lb - la));
                     if (swp) {
                         th_n = xth[po * 32 + od];
                         g_n = xgr[po * 32 + od];

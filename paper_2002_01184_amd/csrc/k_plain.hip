@@ -170,7 +170,7 @@ __device__ __forceinline__ void end_body(const PlainArgs& a, int64_t blk) {
     const double bt = a.ws.beta ? a.ws.beta[c] : 1.0;
     const double dh = (-(bt * lp1) + k1) - a.ws.h0[c];
     const double lar = log_accept_ratio_of(dh);
-    const bool acc = log_accept_uniform(a.key, (uint32_t)c, (uint32_t)t) < lar;
+    const bool acc = accept_below(a.key, (uint32_t)c, (uint32_t)t, lar);
 
     // per-chain select (vectorised where of the paper, Sec. 2.1)
     if (acc)
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(256) void k_remc_exchange(PlainArgs a, int64_t K, i
         const int64_t ca = k * M + m, cb = (k + 1) * M + m;
         const double ba = a.ws.beta ? a.ws.beta[ca] : 1.0, bb = a.ws.beta ? a.ws.beta[cb] : 1.0;
         const double la = a.ws.logp[ca], lb = a.ws.logp[cb];
-        const bool acc = log_uniform52(a.key, (uint32_t)ca, t, TAG_SWAP) < (ba - bb) * (lb - la);
+        const bool acc = log_uniform52_below(a.key, (uint32_t)ca, t, TAG_SWAP, (ba - bb) * (lb - la));
         if (swapped && lane == 0) {
             swapped[ca] = acc ? 1 : 0;
             swapped[cb] = acc ? 1 : 0;
@@ -522,7 +522,7 @@ __global__ __launch_bounds__(256) void k_elem_last(PlainArgs a) {
 
     const double dh = (-(bt * lp1) + k1) - a.ws.h0[c];
     const double lar = log_accept_ratio_of(dh);
-    const bool acc = log_accept_uniform(a.key, (uint32_t)c, (uint32_t)t) < lar;
+    const bool acc = accept_below(a.key, (uint32_t)c, (uint32_t)t, lar);
     const int64_t i = (int64_t)(t - ct.t_begin);
     const bool keep = ct.samples && i >= ct.n_burnin && i < ct.n_burnin + ct.n_results;
     T* smp = keep ? (T*)ct.samples + ((i - ct.n_burnin) * a.C + c) * D : nullptr;
@@ -767,7 +767,7 @@ __global__ __launch_bounds__(64 * DS_NW) void k_dense_step(PlainArgs a) {
     const double h0 = FIRST ? -(bt * lp_old) + s0 : a.ws.h0[c];
     const double dh = (-(bt * sl) + s1) - h0;
     const double lar = log_accept_ratio_of(dh);
-    const bool acc = log_accept_uniform(a.key, (uint32_t)c, (uint32_t)t) < lar;
+    const bool acc = accept_below(a.key, (uint32_t)c, (uint32_t)t, lar);
     const int64_t i = (int64_t)(t - ct.t_begin);
     const bool keep = ct.samples && i >= ct.n_burnin && i < ct.n_burnin + ct.n_results;
     float* smp = keep ? (float*)ct.samples + ((i - ct.n_burnin) * a.C + c) * D : nullptr;
