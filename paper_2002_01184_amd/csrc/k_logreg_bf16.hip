@@ -53,11 +53,23 @@ __device__ __forceinline__ float sigmoid_hw(float s) {
     return __builtin_amdgcn_rcpf(1.0f + e);
 }
 
+// softplus(s) = max(s, 0) + log(1 + e), e = exp(-|s|), in three parts that a kernel
+// can spread over its MFMAs.  Both forms of the logarithm are made and one is
+// selected: a branch a value costs more than the polynomial.  The median with 0
+// and +inf is the maximum with 0 without the compiler's quieting of a NaN (the
+// logarithm's NaN carries on).
+__device__ __forceinline__ float softplus_exp(float s) {
+    return __builtin_amdgcn_exp2f(-1.4426950408889634f * fabsf(s));
+}
+__device__ __forceinline__ float softplus_log(float e) { return __builtin_amdgcn_logf(1.0f + e); }
+__device__ __forceinline__ float softplus_sum(float s, float e, float lg) {
+    const float big = 0.69314718055994531f * lg;
+    const float small = e * (1.0f - e * (0.5f - e * 0.33333333f));
+    return __builtin_amdgcn_fmed3f(s, 0.f, INFINITY) + (e >= 0x1p-10f ? big : small);
+}
 __device__ __forceinline__ float softplus_hw(float s) {
-    const float e = __builtin_amdgcn_exp2f(-1.4426950408889634f * fabsf(s));
-    const float l = e >= 0x1p-10f ? 0.69314718055994531f * __builtin_amdgcn_logf(1.0f + e)
-                                  : e * (1.0f - e * (0.5f - e * 0.33333333f));
-    return fmaxf(s, 0.f) + l;
+    const float e = softplus_exp(s);
+    return softplus_sum(s, e, softplus_log(e));
 }
 
 // eight floats to BF16, round to nearest even (v_cvt_pk_bf16_f32)
@@ -182,19 +194,24 @@ __device__ __forceinline__ void lb_load_theta(const PlainArgs& a, const float* _
 // Gradient partials, software-pipelined: 16 CS chains per wave, NW waves per
 // workgroup (LbGrad: 256 chains per workgroup up to D = 256, so at 8192 chains
 // 32 chain tiles x 8 row splits = one workgroup per CU with each split on its
-// own XCD; two waves per SIMD from D = 33 on).  The residuals of one sub-tile are
-// formed on the vector ALUs while the matrix cores run the other contraction,
-// in three phases per sub-tile s:
-//   1. the X fragments of rows 0..15 of s are read, the residuals of rows
-//      16..31 of s - 1 computed while they arrive, then S of rows 0..15
-//   2. the X fragments of rows 16..31 of s are read; G^T += R^T X^T of s - 1,
-//      with the residuals of rows 0..15 of s computed between its MFMAs
-//   3. S of rows 16..31 of s
-// X^T of sub-tile s - 1 is still read in the iteration of s, so the X^T tiles
-// sit in a ring of NBX + 1 buffers and the X tiles in a ring of NBX (4, or 2
-// beyond D = 256 where two X tiles and three X^T tiles of 32 KB fill the
-// 160 KB); the copies run NBX - 1 sub-tiles ahead.  The labels of a sub-tile are
-// copied beside its X^T tile, or (NBX = 2) read from global memory by each lane.
+// own XCD; two waves per SIMD from D = 33 on).  A sub-tile s is one sequence of
+// 4 KS steps of CS MFMAs: S of its rows 0..15, G^T += R^T X^T of sub-tile s - 1, S
+// of its rows 16..31.  A step also reads the operand fragment of the step PD later,
+// does a slice of the residuals (rows 16..31 of s - 1 in the first part, rows 0..15
+// of s in the second) and, every few steps, issues one copy; scheduling barriers
+// keep the steps apart, since the scheduler, short of registers, had gathered the
+// reads of the G part one by one in front of their MFMAs.
+// Copies and waves meet once per stage of SUBS sub-tiles: one stage is read while
+// the next is copied.  X^T of sub-tile s - 1 is still read in s, so the X^T tiles
+// sit in a ring of one buffer more than the X tiles (beyond D = 256 two X tiles and
+// three X^T tiles of 32 KB fill the 160 KB).  The labels of a sub-tile are copied
+// beside its X^T tile, or (beyond D = 256) read from global memory by each lane.
+//
+// What bounds it: power and the matrix cores.  At D = 256, N = 100000, 8192 chains
+// the MFMAs fill 54% -> 61% of the clocks (3800 -> 3340 a sub-tile), and the clock
+// falls with it, 2.20 -> 2.12 GHz: 704 -> 656 us a gradient (1.28 PFLOP/s).  With
+// half the CUs (50000 rows, 4000 chains) 356 -> 304 us, D = 128 214 -> 190, D = 100
+// (4096 chains) 194 -> 157, D = 500 399 -> 385 (gradient and its finish).
 // ---------------------------------------------------------------------------
 template <int KS>
 struct LbGrad {
@@ -205,10 +222,10 @@ struct LbGrad {
     static constexpr int NW = KS >= 2 ? 8 : 4;
     static constexpr int CS = KS == 1 ? 4 : (KS <= 8 ? 2 : 1);
     static constexpr int CT = NW * 16 * CS;               // chains per workgroup
-    static constexpr int NBX = KS <= 8 ? 4 : 2;           // X buffers
+    static constexpr int SUBS = KS <= 4 ? 4 : (KS <= 8 ? 2 : 1);          // sub-tiles per stage
+    static constexpr int NBX = 2 * SUBS;                  // X buffers
     static constexpr int NBT = NBX + 1;                   // X^T buffers
-    static constexpr int PF = NBX - 1;                    // sub-tiles copied ahead
-    static constexpr bool YLDS = NBX > 2;                 // labels copied to LDS
+    static constexpr bool YLDS = KS <= 8;                 // labels copied to LDS
     static constexpr int DP = 32 * KS;
     static constexpr int XB = LB_RS * DP * 2;             // bytes of an X (or X^T) sub-tile
     static constexpr int TBY = XB + (YLDS ? LD_YB : 0);   // X^T sub-tile + labels
@@ -224,7 +241,7 @@ __device__ __forceinline__ void lr16_grad_body(const PlainArgs& a, const float* 
                                                int nsplit, int blk) {
     using P = LbGrad<KS>;
     constexpr int CS = P::CS, CT = P::CT, NT = 2 * KS, DP = P::DP, XB = P::XB, TBY = P::TBY, XI = P::XI;
-    constexpr int JW = P::JW, J = P::J, PF = P::PF, NBX = P::NBX, NBT = P::NBT, NW = P::NW;
+    constexpr int JW = P::JW, J = P::J, SUBS = P::SUBS, NBX = P::NBX, NBT = P::NBT, NW = P::NW;
     static_assert((2 * XI) % NW == 0, "copies must split evenly over the waves");
     static_assert(P::LDS <= 160 * 1024, "LDS");
     extern __shared__ __align__(16) uint8_t ldsb[];
@@ -256,56 +273,49 @@ __device__ __forceinline__ void lr16_grad_body(const PlainArgs& a, const float* 
     if (r_end > NP) r_end = NP;
     const int nsub = r_begin < r_end ? (int)((r_end - r_begin) / LB_RS) : 0;
 
-    // copies of sub-tile sidx: X into xbase, X^T (and the labels) into tbase
-    auto copy_in = [&](int sidx, uint8_t* __restrict__ xbase, uint8_t* __restrict__ tbase) {
+    // copy k of a wave's J for sub-tile sidx (the last one past the end): X into
+    // xbase, X^T and, as the last copy, the labels into tbase
+    auto copy_k = [&](int sidx, int k, uint8_t* __restrict__ xbase, uint8_t* __restrict__ tbase) {
+        if (sidx >= nsub) sidx = nsub - 1;
         const int64_t r0 = r_begin + (int64_t)sidx * LB_RS;
-        const char* xsrc_t = (const char*)(Xp + r0 * DP);
-        const char* tsrc_t = (const char*)(Xt + r0);
         // the lane index through an empty asm: the per-lane offsets are recomputed
-        // for every sub-tile instead of being hoisted out of the loop (and spilled:
-        // a reload's wait would also wait for the copies in flight)
+        // for every copy instead of being hoisted out of the loop (and spilled: a
+        // reload's wait would also wait for the copies in flight)
         int ln = lane;
         asm volatile("" : "+v"(ln));
-        const uint32_t toff = (uint32_t)(ln >> 2) * (uint32_t)NP * 2u + 16u * (uint32_t)((ln & 3) ^ ((ln >> 3) & 3));
-        // with SR dividing 64 the row of lane ln in copy k is A + (64 NW / SR) k, A below,
-        // with no carry from A's low bits into bit 3, so its swizzle depends on k only
-        // through bit 3 of (64 NW / SR) k -- two offsets per sub-tile
-        constexpr int SR = DP / 8;
-        constexpr bool POW2 = (64 % SR) == 0;
-        constexpr int KSTR = 64 * NW / SR;
-        static_assert(!POW2 || KSTR % 8 == 0 || (KSTR == 4 && NW == 4), "row stride of the copies");
-        uint32_t xo[2] = {0u, 0u};
-        if constexpr (POW2) {
-            const int arow = (64 / SR) * w + ln / SR;
-#pragma unroll
-            for (int par = 0; par < 2; ++par) {
-                const int sw = SR >= 8 ? ((arow & 3) | ((((arow >> 3) & 1) ^ par) << 2)) : (arow & 3);
-                xo[par] = (uint32_t)(ln / SR) * (uint32_t)(DP * 2) + 16u * (uint32_t)((ln % SR) ^ sw);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < JW; ++k) {
-            const int i = w + NW * k;
-            const bool isx = (XI % NW == 0) ? (k < XI / NW) : (i < XI);
-            if (isx) {
-                if constexpr (POW2)
-                    __builtin_amdgcn_global_load_lds((const void*)(xsrc_t + (uint32_t)i * 1024u +
-                                                                   xo[((KSTR * k) >> 3) & 1]),
-                                                     (lds_void_t*)(xbase + i * 1024), 16, 0, 0);
-                else
-                    lb_copy_x_block<KS>(xsrc_t, xbase, i, ln);
-            } else {
-                const int ii = i - XI;
-                __builtin_amdgcn_global_load_lds((const void*)(tsrc_t + (uint32_t)(16 * ii) * (uint32_t)NP * 2u + toff),
-                                                 (lds_void_t*)(tbase + ii * 1024), 16, 0, 0);
-            }
-        }
-        if constexpr (P::YLDS)
+        if (k == JW) {
             __builtin_amdgcn_global_load_lds((const void*)(Yp + r0 + 4 * (ln & 7)), (lds_void_t*)(tbase + XB), 4, 0,
                                              0);
+            return;
+        }
+        const int i = w + NW * k;
+        const bool isx = (XI % NW == 0) ? (k < XI / NW) : (i < XI);
+        if (isx) {
+            // with SR dividing 64 the row of lane ln in copy k is A + (64 NW / SR) k, A
+            // below, with no carry from A's low bits into bit 3, so its swizzle depends
+            // on k only through bit 3 of (64 NW / SR) k
+            constexpr int SR = DP / 8;
+            constexpr bool POW2 = (64 % SR) == 0;
+            constexpr int KSTR = 64 * NW / SR;
+            static_assert(!POW2 || KSTR % 8 == 0 || (KSTR == 4 && NW == 4), "row stride of the copies");
+            const char* src = (const char*)(Xp + r0 * DP);
+            if constexpr (POW2) {
+                const int arow = (64 / SR) * w + ln / SR, par = ((KSTR * k) >> 3) & 1;
+                const int sw = SR >= 8 ? ((arow & 3) | ((((arow >> 3) & 1) ^ par) << 2)) : (arow & 3);
+                const uint32_t xo = (uint32_t)(ln / SR) * (uint32_t)(DP * 2) + 16u * (uint32_t)((ln % SR) ^ sw);
+                __builtin_amdgcn_global_load_lds((const void*)(src + (uint32_t)i * 1024u + xo),
+                                                 (lds_void_t*)(xbase + i * 1024), 16, 0, 0);
+            } else {
+                lb_copy_x_block<KS>(src, xbase, i, ln);
+            }
+        } else {
+            const int ii = i - XI;
+            const uint32_t toff = (uint32_t)(ln >> 2) * (uint32_t)NP * 2u + 16u * (uint32_t)((ln & 3) ^ ((ln >> 3) & 3));
+            __builtin_amdgcn_global_load_lds(
+                (const void*)((const char*)(Xt + r0) + (uint32_t)(16 * ii) * (uint32_t)NP * 2u + toff),
+                (lds_void_t*)(tbase + ii * 1024), 16, 0, 0);
+        }
     };
-    auto xbuf = [&](int sidx) { return xring + (sidx % NBX) * XB; };
-    auto tbuf = [&](int sidx) { return tring + (sidx % NBT) * TBY; };
     // labels of the lane's rows 8 g .. 8 g + 7 of sub-tile sidx
     auto labels = [&](int sidx, const uint8_t* tb) {
         if constexpr (P::YLDS) return *(const uint2*)(tb + XB + 8 * g);
@@ -325,6 +335,22 @@ __device__ __forceinline__ void lr16_grad_body(const PlainArgs& a, const float* 
         for (int v = 0; v < 4; ++v) r[v] = (float)((yw >> (8 * v)) & 0xffu) - sigmoid_hw(sv[v]);
         return pack4_bf16(r);
     };
+    // The part of step `st` of n in the same residuals of CS halves, one element a lane
+    // after the other from step `first` on, over `span` steps: the exponential, the
+    // reciprocal and the difference in three consecutive steps (the last step takes
+    // what is left); r[cs] holds the values between.
+    auto resid_slice = [&](int st, int n, int first, int span, const floatx4* sv, uint32_t yw, floatx4* r) {
+        constexpr int E = 4 * CS;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int cs = e / 4, v = e % 4;
+            auto at = [&](int k) { const int t = first + e * span / E + k; return (t < n ? t : n - 1) == st; };
+            if (at(0)) r[cs][v] = __builtin_amdgcn_exp2f(-1.4426950408889634f * sv[cs][v]);
+            if (at(1)) r[cs][v] = __builtin_amdgcn_rcpf(1.0f + r[cs][v]);
+            if (at(2)) r[cs][v] = (float)((yw >> (8 * v)) & 0xffu) - r[cs][v];
+        }
+    };
+    constexpr int PD = KS == 1 ? 2 : 4;                                  // fragments read ahead of the MFMAs
     // S of one half from fragments read ahead (all of them up to KS = 8, else
     // eight in flight)
     constexpr int FA = KS < 8 ? KS : 8;
@@ -365,99 +391,120 @@ __device__ __forceinline__ void lr16_grad_body(const PlainArgs& a, const float* 
         }
     };
 
-#pragma unroll
-    for (int t = 0; t < PF; ++t)
-        if (t < nsub) copy_in(t, xbuf(t), tbuf(t));
-    // sub-tile sidx complete: the copies of the following PF - 1 may stay outstanding
-    auto wait_tile = [&](int sidx) {
-        if constexpr (PF >= 3) {
-            if (sidx + 2 < nsub) wait_vmcnt<2 * J>();
-            else if (sidx + 1 < nsub) wait_vmcnt<J>();
-            else wait_vmcnt<0>();
-        } else if constexpr (PF == 2) {
-            if (sidx + 1 < nsub) wait_vmcnt<J>();
-            else wait_vmcnt<0>();
-        } else {
-            wait_vmcnt<0>();
-        }
-        lds_barrier();
-    };
-
     // pipeline registers: S of rows 16..31 of the previous sub-tile, the packed
     // residuals of its rows 0..15 and its labels of rows 16..31
     floatx4 s1p[CS];
     uint2 lo_p[CS];
     uint32_t yp1 = 0u;
-    if (nsub > 0) {       // the first sub-tile: no G of a previous one
-        wait_tile(0);
-        const uint2 yl = labels(0, tbuf(0));
-        if (PF < nsub) copy_in(PF, xbuf(PF), tbuf(PF));
-        yp1 = yl.y;
+    // the first sub-tile: no G of a previous one
+    auto head = [&](const uint8_t* __restrict__ xb, const uint8_t* __restrict__ tcur) {
+        const uint2 yl = labels(0, tcur);
         floatx4 s0[CS];
-        sphase(xbuf(0), xoff[0], s0);
+        sphase(xb, xoff[0], s0);
 #pragma unroll
         for (int cs = 0; cs < CS; ++cs) lo_p[cs] = resid(s0[cs], yl.x);
-        sphase(xbuf(0), xoff[1], s1p);
-    }
-    // one sub-tile; the copy targets (xdst, tdst) and the buffers read (xb, tprev,
-    // tcur) are distinct, which the restrict qualifiers tell the compiler, so the
-    // LDS reads need not wait for the copies in flight (the explicit vmcnt waits
-    // and the barrier order the sub-tiles)
-    auto iter = [&](int sidx, uint8_t* __restrict__ xdst, uint8_t* __restrict__ tdst, const uint8_t* __restrict__ xb,
-                    const uint8_t* __restrict__ tprev, const uint8_t* __restrict__ tcur) {
-        // the labels first: a global read of them then waits only on older copies
+        sphase(xb, xoff[1], s1p);
+        yp1 = yl.y;
+    };
+    // copies of sub-tile sn, one every few steps of another's MFMAs: the address units
+    // take 16 clocks a copy, and in a burst behind the barrier the waves stood at them
+    // for 600 clocks a sub-tile (D = 256)
+    auto spread_copy = [&](int st, int sn, uint8_t* xw, uint8_t* tw) {
+        static_assert(J <= 2 * KS, "one copy a step");
+        const int k = (st * J + 2 * KS - 1) / (2 * KS);
+        if (k < J && (k * 2 * KS) / J == st) copy_k(sn, k, xw + (sn % NBX) * XB, tw + (sn % NBT) * TBY);
+    };
+    // One sub-tile, and the copies of the sub-tile SUBS later into buffers that no
+    // wave reads before the next stage's barrier (past the end, the last sub-tile
+    // again).  The copies write through xw and tw and the sub-tile reads through xr
+    // and tr, which are restrict: the LDS reads need not wait for the copies in
+    // flight (the vmcnt wait and the barrier between stages order them).
+    auto step = [&](int sidx, uint8_t* __restrict__ xw, uint8_t* __restrict__ tw, const uint8_t* __restrict__ xr,
+                    const uint8_t* __restrict__ tr) {
+        const uint8_t* xb = xr + (sidx % NBX) * XB;
+        const uint8_t* tprev = tr + ((sidx + NBT - 1) % NBT) * TBY;
+        const uint8_t* tcur = tr + (sidx % NBT) * TBY;
         const uint2 yl = labels(sidx, tcur);
-        if (sidx + PF < nsub) copy_in(sidx + PF, xdst, tdst);
-        // phase 1; a phase's base offsets pass through one empty asm at its start, so
-        // that a register per offset plus immediate offsets address its fragments
-        uint32_t o1[2] = {xoff[0][0], xoff[0][1]};
+        // a phase's base offsets pass through one empty asm at its start, so that a
+        // register per offset plus immediate offsets address its fragments
+        uint32_t o1[2] = {xoff[0][0], xoff[0][1]}, o2[2] = {xoff[1][0], xoff[1][1]}, ot = toff_f;
+        auto frag = [&](int st) {
+            if (st < KS) return xfrag(xb, o1, st);
+            if (st < 3 * KS) return *(const bf16x8*)(tprev + ot + 1024 * (st - KS));
+            return xfrag(xb, o2, st - 3 * KS);
+        };
         asm volatile("" : "+v"(o1[0]), "+v"(o1[1]));
-        bf16x8 xa[FA];
+        bf16x8 fr[PD];
 #pragma unroll
-        for (int ks = 0; ks < FA; ++ks) xa[ks] = xfrag(xb, o1, ks);
+        for (int st = 0; st < PD; ++st) {
+            if (st == KS) asm volatile("" : "+v"(ot));
+            if (st == 3 * KS) asm volatile("" : "+v"(o2[0]), "+v"(o2[1]));
+            fr[st] = frag(st);
+        }
+        floatx4 s0[CS], hi[CS], lo[CS];
         bf16x8 rp[CS];
 #pragma unroll
-        for (int cs = 0; cs < CS; ++cs) {
-            const uint2 hi = resid(s1p[cs], yp1);
-            rp[cs] = __builtin_bit_cast(bf16x8, make_uint4(lo_p[cs].x, lo_p[cs].y, hi.x, hi.y));
-        }
-        floatx4 s0[CS];
+        for (int st = 0; st < 4 * KS; ++st) {
+            const bf16x8 f = fr[st % PD];
+            // the wave in its G phase goes before the SIMD's other one
+            if (KS <= 8 && st == KS) __builtin_amdgcn_s_setprio(1);
+            if (KS <= 8 && st == 3 * KS) __builtin_amdgcn_s_setprio(0);
 #pragma unroll
-        for (int cs = 0; cs < CS; ++cs) s0[cs] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int cs = 0; cs < CS; ++cs) {
+                const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+                if (st < KS)
+                    s0[cs] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, thb[cs][st], st == 0 ? zero : s0[cs], 0, 0, 0);
+                else if (st < 3 * KS)
+                    gacc[cs][st - KS] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rp[cs], f, gacc[cs][st - KS], 0, 0, 0);
+                else
+                    s1p[cs] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, thb[cs][st - 3 * KS],
+                                                                      st == 3 * KS ? zero : s1p[cs], 0, 0, 0);
+            }
+            if (st + PD < 4 * KS) {
+                if (st + PD == KS) asm volatile("" : "+v"(ot));
+                if (st + PD == 3 * KS) asm volatile("" : "+v"(o2[0]), "+v"(o2[1]));
+                fr[st % PD] = frag(st + PD);
+            }
+            if (st < KS) {
+                resid_slice(st, KS, 0, KS > 3 ? KS - 3 : 1, s1p, yp1, hi);
+                if (st == KS - 1)
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const bf16x8 ax = xa[ks % FA];
-            if (ks + FA < KS) xa[ks % FA] = xfrag(xb, o1, ks + FA);
+                    for (int cs = 0; cs < CS; ++cs) {
+                        const uint2 h = pack4_bf16(hi[cs]);
+                        rp[cs] = __builtin_bit_cast(bf16x8, make_uint4(lo_p[cs].x, lo_p[cs].y, h.x, h.y));
+                    }
+            } else if (st < 3 * KS) {
+                resid_slice(st - KS, 2 * KS, 1, KS > 1 ? 2 * KS - 3 : 1, s0, yl.x, lo);
+                if (st == 3 * KS - 1)
 #pragma unroll
-            for (int cs = 0; cs < CS; ++cs)
-                s0[cs] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ax, thb[cs][ks], s0[cs], 0, 0, 0);
-        }
-        // phase 2
-        uint32_t o2[2] = {xoff[1][0], xoff[1][1]}, ot = toff_f;
-        asm volatile("" : "+v"(o2[0]), "+v"(o2[1]), "+v"(ot));
-        bf16x8 xb1[FA];
-#pragma unroll
-        for (int ks = 0; ks < FA; ++ks) xb1[ks] = xfrag(xb, o2, ks);
-        gphase(tprev, rp, ot);
-#pragma unroll
-        for (int cs = 0; cs < CS; ++cs) lo_p[cs] = resid(s0[cs], yl.x);
-        // phase 3
-#pragma unroll
-        for (int cs = 0; cs < CS; ++cs) s1p[cs] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const bf16x8 ax = xb1[ks % FA];
-            if (ks + FA < KS) xb1[ks % FA] = xfrag(xb, o2, ks + FA);
-#pragma unroll
-            for (int cs = 0; cs < CS; ++cs)
-                s1p[cs] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ax, thb[cs][ks], s1p[cs], 0, 0, 0);
+                    for (int cs = 0; cs < CS; ++cs) lo_p[cs] = pack4_bf16(lo[cs]);
+            }
+            spread_copy(st, sidx + SUBS, xw, tw);
+            if (KS > 1 && (st & 1)) __builtin_amdgcn_sched_barrier(0);
         }
         yp1 = yl.y;
     };
-    for (int sidx = 1; sidx < nsub; ++sidx) {
-        wait_tile(sidx);
-        iter(sidx, xbuf(sidx + PF), tbuf(sidx + PF), xbuf(sidx), tbuf(sidx + NBT - 1), tbuf(sidx));
+    if (nsub > 0) {
+#pragma unroll
+        for (int u = 0; u < 2 * SUBS; ++u) {
+#pragma unroll
+            for (int k = 0; k < J; ++k)
+                if (u <= SUBS) copy_k(u, k, xring + (u % NBX) * XB, tring + (u % NBT) * TBY);
+            if (u == SUBS - 1) {
+                wait_vmcnt<0>();       // the only copies outstanding are the first stage's
+                lds_barrier();
+            }
+        }
+        head(xring, tring);
     }
+    for (int sidx = 1; sidx < nsub; ++sidx) {
+        if (sidx % SUBS == 0) {
+            wait_vmcnt<0>();
+            lds_barrier();
+        }
+        step(sidx, xring, tring, xring, tring);
+    }
+    wait_vmcnt<0>();                   // no copy may land in LDS after the end
     if (nsub > 0) {
         bf16x8 rp[CS];
 #pragma unroll
@@ -465,7 +512,7 @@ __device__ __forceinline__ void lr16_grad_body(const PlainArgs& a, const float* 
             const uint2 hi = resid(s1p[cs], yp1);
             rp[cs] = __builtin_bit_cast(bf16x8, make_uint4(lo_p[cs].x, lo_p[cs].y, hi.x, hi.y));
         }
-        gphase(tbuf(nsub - 1), rp, toff_f);
+        gphase(tring + ((nsub - 1) % NBT) * TBY, rp, toff_f);
     }
 #pragma unroll
     for (int cs = 0; cs < CS; ++cs)
@@ -482,18 +529,19 @@ __device__ __forceinline__ void lr16_grad_body(const PlainArgs& a, const float* 
 // ---------------------------------------------------------------------------
 // Accurate log-probability partials: theta = hi + mid + lo (three BF16 terms,
 // smallest first), 16 chains per wave, each X fragment feeding 3 MFMAs; the
-// softplus terms summed per chain in FP64.  Pipelined
-// like the gradient: the softplus of one 16-row half is computed while the
-// fragments of the next half arrive and before its MFMAs.  X tiles (with their
-// labels) in a ring of four buffers, copies three sub-tiles ahead.
+// softplus terms summed per chain in FP64.  Steps like the gradient's: the terms of
+// one 16-row half are formed in slices between the MFMAs of the next one (before,
+// with a branch a value, MFMAs and terms took turns: 3500 clocks a sub-tile, 1540
+// of them MFMAs).  D = 256, N = 100000, 8192 chains 1150 -> 1010 us, D = 128
+// 393 -> 317 us.
 // ---------------------------------------------------------------------------
 template <int KS>
 struct LbLogp {
     // eight waves of 16 chains (two waves per SIMD)
     static constexpr int NW = 8;
-    static constexpr int CS = 1;
-    static constexpr int CT = NW * 16 * CS;
-    static constexpr int NB = 4;
+    static constexpr int CT = NW * 16;
+    static constexpr int SUBS = 2;                        // sub-tiles per stage
+    static constexpr int NB = 2 * SUBS;
     static constexpr int DP = 32 * KS;
     static constexpr int XB = LB_RS * DP * 2;
     static constexpr int BUF = XB + LD_YB;
@@ -519,7 +567,7 @@ template <int KS>
 __device__ __forceinline__ void lr16_logp_body(const PlainArgs& a, const float* __restrict__ xsrc,
                                                int64_t rows_per_split, int nsplit, int blk) {
     using P = LbLogp<KS>;
-    constexpr int CS = P::CS, CT = P::CT, NB = P::NB, XB = P::XB, BUF = P::BUF, XI = P::XI, JW = P::JW, J = P::J;
+    constexpr int CT = P::CT, SUBS = P::SUBS, NB = P::NB, XB = P::XB, BUF = P::BUF, XI = P::XI, JW = P::JW, J = P::J;
     constexpr int DP = P::DP;
     static_assert(P::LDS <= 160 * 1024, "LDS");
     extern __shared__ __align__(16) uint8_t ldsb[];
@@ -530,124 +578,132 @@ __device__ __forceinline__ void lr16_logp_body(const PlainArgs& a, const float* 
     lb_map(blk, ntile, nsplit, &tile, &split);
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, g = lane >> 4;
-    const int64_t cw = (int64_t)tile * CT + 16 * CS * w;
+    const int64_t cw = (int64_t)tile * CT + 16 * w;
     const uint16_t* Xp = (const uint16_t*)a.ws.xp;
     const uint8_t* Yp = (const uint8_t*)a.ws.yp;
 
-    // theta = hi + mid + lo, three BF16 B operands per chain tile and k-step
-    bf16x8 th[3][CS][KS];
-#pragma unroll
-    for (int cs = 0; cs < CS; ++cs) {
+    // theta = hi + mid + lo, three BF16 B operands per k-step
+    bf16x8 th[3][KS];
+    {
         floatx8 v[KS];
-        lb_load_theta<KS>(a, xsrc, nullptr, 0, cw + 16 * cs + l16, g, v);
+        lb_load_theta<KS>(a, xsrc, nullptr, 0, cw + l16, g, v);
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) lb_split_theta(v[ks], th[0][cs][ks], th[1][cs][ks], th[2][cs][ks]);
+        for (int ks = 0; ks < KS; ++ks) lb_split_theta(v[ks], th[0][ks], th[1][ks], th[2][ks]);
     }
     const int64_t r_begin = (int64_t)split * rows_per_split;
     int64_t r_end = r_begin + rows_per_split;
     if (r_end > NP) r_end = NP;
     const int nsub = r_begin < r_end ? (int)((r_end - r_begin) / LB_RS) : 0;
 
-    auto copy_in = [&](int sidx, uint8_t* __restrict__ base) {
+    // copy k of a wave's J for sub-tile sidx (the last one past the end)
+    auto copy_k = [&](int sidx, int k, uint8_t* __restrict__ base) {
+        if (sidx >= nsub) sidx = nsub - 1;
         const int64_t r0 = r_begin + (int64_t)sidx * LB_RS;
-        const char* xsrc_t = (const char*)(Xp + r0 * DP);
         int ln = lane;
         asm volatile("" : "+v"(ln));
-#pragma unroll
-        for (int k = 0; k < JW; ++k) {
-            int i = w + P::NW * k;
-            if (i >= XI) i = XI - 1;          // a repeated copy keeps the count equal over the waves
-            lb_copy_x_block<KS>(xsrc_t, base, i, ln);
+        if (k == JW) {
+            __builtin_amdgcn_global_load_lds((const void*)(Yp + r0 + 4 * (ln & 7)), (lds_void_t*)(base + XB), 4, 0, 0);
+            return;
         }
-        __builtin_amdgcn_global_load_lds((const void*)(Yp + r0 + 4 * (ln & 7)), (lds_void_t*)(base + XB), 4, 0, 0);
+        int i = w + P::NW * k;
+        if (i >= XI) i = XI - 1;          // a repeated copy keeps the count equal over the waves
+        lb_copy_x_block<KS>((const char*)(Xp + r0 * DP), base, i, ln);
     };
     uint32_t xoff[2][2];
     lb_xfrag_offsets<KS>(l16, g, xoff);
     auto xfrag = [&](const uint8_t* xb, const uint32_t* o2, int ks) {
         return *(const bf16x8*)(xb + o2[ks & 1] + 128 * (ks >> 1));
     };
-    // log-likelihood terms of one half, y s - softplus(s), for the lane's rows
-    // row0 + v (rows at or past N skipped when the sub-tile reaches them); a
-    // lane's four terms are added in FP32 before the FP64 sum (a rounding of
-    // about 1e-7 of a few terms, far below what the accept test resolves)
-    double lp[CS] = {};
-    auto accum = [&](const floatx4* sv, uint32_t yw, int64_t row0) {
-        const bool whole = row0 + 4 <= N;
+    // Log-likelihood terms of one half, y s - softplus(s), for the lane's rows 0..3
+    // (those at or past `left` skipped: the data's end), in slices like the
+    // gradient's residuals; a lane's four terms are added in FP32 before the FP64
+    // sum (a rounding of about 1e-7 of a few terms, far below what the accept test
+    // resolves).
+    double lp = 0.0;
+    float ex[4], lg[4], t4 = 0.f;
+    auto term_slice = [&](int st, int n, const floatx4& sv, uint32_t yw, int left) {
+        const int first = n > 4 ? 1 : 0, span = n > 4 ? n - 3 : 1;
 #pragma unroll
-        for (int cs = 0; cs < CS; ++cs) {
-            float t4 = 0.f;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float s = sv[cs][v];
-                const float y = (float)((yw >> (8 * v)) & 0xffu);
-                const float t = fmaf(y, s, -softplus_hw(s));
-                t4 += (whole || row0 + v < N) ? t : 0.f;
+        for (int v = 0; v < 4; ++v) {
+            // KS = 16: theta leaves no registers for values between steps
+            auto at = [&](int k) { const int t = first + v * span / 4 + (KS > 12 ? 0 : k); return (t < n ? t : n - 1) == st; };
+            if (at(0)) ex[v] = softplus_exp(sv[v]);
+            if (at(1)) lg[v] = softplus_log(ex[v]);
+            if (at(2)) {
+                const float t = fmaf((float)((yw >> (8 * v)) & 0xffu), sv[v], -softplus_sum(sv[v], ex[v], lg[v]));
+                const float tm = v < left ? t : 0.f;
+                t4 = v == 0 ? tm : t4 + tm;
             }
-            lp[cs] += (double)t4;
         }
+        if (st == n - 1) lp += (double)t4;
     };
-    constexpr int FA = KS < 8 ? KS : 8;
-    auto shalf = [&](const uint8_t* __restrict__ xb, const uint32_t* o2, floatx4* sacc) {
-#pragma unroll
-        for (int cs = 0; cs < CS; ++cs) sacc[cs] = floatx4{0.f, 0.f, 0.f, 0.f};
-        bf16x8 xa[FA];
-#pragma unroll
-        for (int ks = 0; ks < FA; ++ks) xa[ks] = xfrag(xb, o2, ks);
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const bf16x8 ax = xa[ks % FA];
-            if (ks + FA < KS) xa[ks % FA] = xfrag(xb, o2, ks + FA);
-#pragma unroll
-            for (int term = 2; term >= 0; --term)
-#pragma unroll
-                for (int cs = 0; cs < CS; ++cs)
-                    sacc[cs] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ax, th[term][cs][ks], sacc[cs], 0, 0, 0);
-        }
-    };
-
-#pragma unroll
-    for (int t = 0; t < NB - 1; ++t)
-        if (t < nsub) copy_in(t, ldsb + t * BUF);
-    floatx4 sprev[CS];
+    constexpr int PD = KS == 1 || KS > 12 ? 2 : 4;         // fragments read ahead of the MFMAs (KS = 16: theta fills the registers)
+    floatx4 sprev = {0.f, 0.f, 0.f, 0.f};                  // S of the previous half, its labels and rows left
     uint32_t yprev = 0u;
-    int64_t rowprev = 0;
-    bool have_prev = false;
-    auto step = [&](int sidx, uint8_t* __restrict__ nxt, const uint8_t* __restrict__ base) {
-        if (sidx + NB - 1 < nsub) copy_in(sidx + NB - 1, nxt);
-        const int64_t r0 = r_begin + (int64_t)sidx * LB_RS;
-        const uint2 yl = *(const uint2*)(base + XB + 8 * g);
-        // half 0 of this sub-tile, with the previous half's softplus while its fragments arrive
-        uint32_t o1[2] = {xoff[0][0], xoff[0][1]};
+    int lprev = 0;
+    // One sub-tile, and the copies of the one SUBS later; reads and copies through
+    // restrict pointers as in the gradient.
+    auto step = [&](int sidx, uint8_t* __restrict__ xw, const uint8_t* __restrict__ xr) {
+        const uint8_t* xb = xr + (sidx % NB) * BUF;
+        const int64_t rest = N - (r_begin + (int64_t)sidx * LB_RS);
+        const uint2 yl = *(const uint2*)(xb + XB + 8 * g);
+        const int left = (int)(rest < LB_RS ? rest : LB_RS) - 8 * g;
+        uint32_t o1[2] = {xoff[0][0], xoff[0][1]}, o2[2] = {xoff[1][0], xoff[1][1]};
+        auto frag = [&](int st) { return st < KS ? xfrag(xb, o1, st) : xfrag(xb, o2, st - KS); };
         asm volatile("" : "+v"(o1[0]), "+v"(o1[1]));
-        floatx4 s0[CS];
-        if (have_prev) accum(sprev, yprev, rowprev);
-        shalf(base, o1, s0);
-        // half 1, with half 0's softplus
-        uint32_t o2[2] = {xoff[1][0], xoff[1][1]};
-        asm volatile("" : "+v"(o2[0]), "+v"(o2[1]));
-        accum(s0, yl.x, r0 + 8 * g);
-        shalf(base, o2, sprev);
-        yprev = yl.y;
-        rowprev = r0 + 8 * g + 4;
-        have_prev = true;
-    };
-    for (int sidx = 0; sidx < nsub; ++sidx) {
-        if (sidx + 2 < nsub) wait_vmcnt<2 * J>();
-        else if (sidx + 1 < nsub) wait_vmcnt<J>();
-        else wait_vmcnt<0>();
-        lds_barrier();
-        step(sidx, ldsb + ((sidx + NB - 1) % NB) * BUF, ldsb + (sidx % NB) * BUF);
-    }
-    if (have_prev) accum(sprev, yprev, rowprev);
-    // lanes holding chain l16: l16, l16 + 16, + 32, + 48
+        bf16x8 fr[PD];
 #pragma unroll
-    for (int cs = 0; cs < CS; ++cs) {
-        double v = lp[cs];
-        v += __shfl_xor(v, 16, 64);
-        v += __shfl_xor(v, 32, 64);
-        const int64_t c = cw + 16 * cs + l16;
-        if (g == 0 && c < C) a.ws.part_lp[(int64_t)split * C + c] = v;
+        for (int st = 0; st < PD; ++st) {
+            if (st == KS) asm volatile("" : "+v"(o2[0]), "+v"(o2[1]));
+            fr[st] = frag(st);
+        }
+        floatx4 sh[2];
+#pragma unroll
+        for (int st = 0; st < 2 * KS; ++st) {
+            const int h = st / KS, ks = st % KS;
+            const bf16x8 f = fr[st % PD];
+#pragma unroll
+            for (int term = 2; term >= 0; --term) {
+                const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+                sh[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, th[term][ks], ks == 0 && term == 2 ? zero : sh[h], 0, 0,
+                                                                0);
+            }
+            if (st + PD < 2 * KS) {
+                if (st + PD == KS) asm volatile("" : "+v"(o2[0]), "+v"(o2[1]));
+                fr[st % PD] = frag(st + PD);
+            }
+            if (h == 0) term_slice(ks, KS, sprev, yprev, lprev);
+            else term_slice(ks, KS, sh[0], yl.x, left);
+            const int k = (st * J + KS - 1) / KS;
+            if (k < J && (k * KS) / J == st) copy_k(sidx + SUBS, k, xw + ((sidx + SUBS) % NB) * BUF);
+            if (J > KS && st == 0) copy_k(sidx + SUBS, 1, xw + ((sidx + SUBS) % NB) * BUF);
+            if (st & 1) __builtin_amdgcn_sched_barrier(0);
+        }
+        sprev = sh[1];
+        yprev = yl.y;
+        lprev = left - 4;
+    };
+    if (nsub > 0) {
+#pragma unroll
+        for (int u = 0; u < SUBS; ++u)
+#pragma unroll
+            for (int k = 0; k < J; ++k) copy_k(u, k, ldsb + u * BUF);
     }
+    for (int sidx = 0; sidx < nsub; ++sidx) {
+        if (sidx % SUBS == 0) {
+            wait_vmcnt<0>();               // the only copies outstanding are this stage's
+            lds_barrier();
+        }
+        step(sidx, ldsb, ldsb);
+    }
+    wait_vmcnt<0>();                       // no copy may land in LDS after the end
+#pragma unroll
+    for (int st = 0; st < 3; ++st) term_slice(st, 3, sprev, yprev, lprev);
+    // lanes holding chain l16: l16, l16 + 16, + 32, + 48
+    lp += __shfl_xor(lp, 16, 64);
+    lp += __shfl_xor(lp, 32, 64);
+    const int64_t c = cw + l16;
+    if (g == 0 && c < C) a.ws.part_lp[(int64_t)split * C + c] = lp;
 }
 
 // lpq[c] = sum over splits (fixed order) of the log-probability partials
