@@ -1263,7 +1263,7 @@ static hipError_t lb_grad_k(const PlainArgs& a, const float* x, const float* p, 
     // one's).  Per gradient and its partial sum: 20011 x 150, 200 chains 140 -> 32 us;
     // 30000 x 250, 1000 chains 255 -> 76, 2000 chains 260 -> 115, 3000 chains 265 ->
     // 214; 30000 x 512, 2048 chains 274 -> 195.  Past the line: 50000 x 256, 4000
-    // chains 350 in two rounds against 357; 30000 x 512, 3000 chains 342 against 293.
+    // chains 350 in two rounds against 304; 30000 x 512, 3000 chains 342 against 293.
     auto blocks = [&](int cs) { return (a.C + 16 * cs - 1) / (16 * cs) * nsplit; };
     if (blocks(1) <= 256) return lb_few_launch<KS, 1>(a, x, p, drift, nsplit, rows, s);
     if (blocks(2) <= 256) return lb_few_launch<KS, 2>(a, x, p, drift, nsplit, rows, s);
