@@ -18,7 +18,7 @@
 //
 // Against the FP32-MFMA kernel before it, per leapfrog step with its partial
 // sum, and the gradient's error against 64 bits (2-norm, one step, before and
-// after): 100000 x 256, BF16 X, 2048 chains 2618 -> 560 us, 9.8e-7 -> 6.1e-7;
+// after): 100000 x 256, BF16 X, 2048 chains 2618 -> 523 us, 9.8e-7 -> 6.1e-7;
 // 20000 x 400, BF16 X, 2000 chains 1401 -> 370 us, 1.5e-6 -> 6.6e-7; 5000 x 300,
 // FP32 X, 700 chains 325 -> 84 us, 1.4e-6 -> 4.9e-7; 10000 x 25, FP32 X, 1024
 // chains 86 -> 28.5 us, 3.1e-7 -> 2.4e-7.  At 100000 x 256 the MFMAs take 0.28
@@ -351,14 +351,39 @@ __global__ __launch_bounds__(64 * LS_NW, ls_wps(KS)) void k_lr32_step(
                 sh[h] = floatx4{0.f, 0.f, 0.f, 0.f};
                 sl[h] = floatx4{0.f, 0.f, 0.f, 0.f};
             }
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                bf16x8 xa[2][XT];
+            // Operand fragments are read a step ahead where the registers allow; the
+            // scheduling barriers keep the reads there (the scheduler, short of
+            // registers, gathers them in front of their own MFMAs), and the wave in its
+            // G part goes before the SIMD's other one.  100000 x 256, 2048 chains: 549 ->
+            // 523 us a gradient with its finish; 30000 x 128, 4096 chains 202 -> 198.
+            // Elsewhere the second set of fragments spills or waves leave (400 dims 201
+            // -> 220) or nothing changes (20 dims 106, X in FP32 at 128 dims 221 -> 222).
+            constexpr int RD = XT == 1 && KS >= 4 && KS <= 8 && !LOGP ? 2 : 1;
+            auto read_x = [&](int ks, bf16x8 (&xa)[2][XT]) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
 #pragma unroll
                     for (int t = 0; t < XT; ++t)
                         xa[h][t] = *(const bf16x8*)(buf + xo[ks & 1] + 128 * (ks >> 1) + h * 16 * RB + t * PLANE);
+            };
+            auto read_t = [&](int n0, bf16x8 (&xt)[2][XT]) {
+#pragma unroll
+                for (int n = 0; n < 2; ++n)
+#pragma unroll
+                    for (int t = 0; t < XT; ++t) {
+                        const uint8_t* p = buf + to[(n0 + n) & 3] + 128 * ((n0 + n) >> 2) + t * PLANE;
+                        const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+                        const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 16 * RB));
+                        xt[n][t] = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
+                    }
+            };
+            bf16x8 xf[RD][2][XT];
+            if (RD == 2) read_x(0, xf[0]);
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                if (RD == 1) read_x(ks, xf[0]);
+                else if (ks + 1 < KS) read_x(ks + 1, xf[(ks + 1) % RD]);
+                const bf16x8(&xa)[2][XT] = xf[ks % RD];
 #define LS_MFMA(A, B, ACC) ACC = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B, ACC, 0, 0, 0)
 #pragma unroll
                 for (int i = 0; i < (XT == 1 ? 2 : 7); ++i) {
@@ -371,7 +396,9 @@ __global__ __launch_bounds__(64 * LS_NW, ls_wps(KS)) void k_lr32_step(
 #pragma unroll
                         for (int h = 0; h < 2; ++h) LS_MFMA(xa[h][0], th[0][ks], sh[h]);
                 }
+                if (RD == 2) __builtin_amdgcn_sched_barrier(0);
             }
+            if (RD == 2) read_t(0, xf[0]);
             const uint32_t* yl = (const uint32_t*)(buf + XT * PLANE) + 4 * g;
             // residuals y - sigmoid(s) = y ? sigmoid(-s) : -sigmoid(s), split into three
             // BF16 terms; rows past the split are zero in X and add nothing to G
@@ -407,18 +434,12 @@ __global__ __launch_bounds__(64 * LS_NW, ls_wps(KS)) void k_lr32_step(
             rb[1] = packed(rm);
             rb[2] = packed(rl);
             // G += X^T R, two dim tiles at a time
+            if (RD == 2) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
             for (int n0 = 0; n0 < NT; n0 += 2) {
-                bf16x8 xt[2][XT];
-#pragma unroll
-                for (int n = 0; n < 2; ++n)
-#pragma unroll
-                    for (int t = 0; t < XT; ++t) {
-                        const uint8_t* p = buf + to[(n0 + n) & 3] + 128 * ((n0 + n) >> 2) + t * PLANE;
-                        const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
-                        const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 16 * RB));
-                        xt[n][t] = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
-                    }
+                if (RD == 1) read_t(n0, xf[0]);
+                else if (n0 + 2 < NT) read_t(n0 + 2, xf[(n0 / 2 + 1) % RD]);
+                const bf16x8(&xt)[2][XT] = xf[(n0 / 2) % RD];
 #pragma unroll
                 for (int i = 0; i < (XT == 1 ? 3 : 8); ++i) {
                     constexpr int XI[8] = {2, 1, 2, 0, 1, 1, 0, 0}, TI[8] = {1, 2, 0, 2, 1, 0, 1, 0};
@@ -426,8 +447,10 @@ __global__ __launch_bounds__(64 * LS_NW, ls_wps(KS)) void k_lr32_step(
 #pragma unroll
                     for (int n = 0; n < 2; ++n) LS_MFMA(xt[n][xi], rb[ti], gacc[n0 + n]);
                 }
+                if (RD == 2) __builtin_amdgcn_sched_barrier(0);
             }
 #undef LS_MFMA
+            if (RD == 2) __builtin_amdgcn_s_setprio(0);
         }
         if (NB == 1 && st + 1 < nst) {
             __syncthreads();
