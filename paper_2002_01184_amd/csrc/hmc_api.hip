@@ -45,6 +45,8 @@ struct hmc_ctx {
     int32_t form;            // effective form
     hipGraphExec_t graph_exec;
     bool graph_ready;
+    bool boot_steps;         // the state's gradient and logp come from the plain form's step kernel
+    uint64_t t_boot;         // t at the last bootstrap
     hmc::KernelTimer timer;  // armed by hmc_kernel_timer_start (a.timer points here)
 };
 
@@ -227,6 +229,14 @@ static hmc_status check_init_args(const hmc_target* target, const hmc_config* co
     return HMC_OK;
 }
 
+// The gradient and logp at x_src (copied in; NULL: the state as it is), by the
+// kernels that transitions of the context's form continue with.
+static hmc_status bootstrap(hmc_ctx* ctx, const void* x_src) {
+    ctx->boot_steps = ctx->form != HMC_FORM_FUSED;
+    ctx->t_boot = ctx->t;
+    return check_hip(launch_bootstrap(ctx->a, x_src, ctx->boot_steps, ctx->stream), "bootstrap");
+}
+
 // hmc_init's device work on a context the caller owns: carve the workspace,
 // pick the form, upload step sizes, bootstrap.  Arguments already checked.
 static hmc_status init_ctx(hmc_ctx* ctx, const TargetDev& t, const hmc_config* config, const void* init_state,
@@ -260,7 +270,7 @@ static hmc_status init_ctx(hmc_ctx* ctx, const TargetDev& t, const hmc_config* c
     if (st == HMC_OK && a.bf16_grad) st = check_hip(launch_pad_bf16(a, ctx->stream), "padded copies of X");
     if (st == HMC_OK) st = check_hip(launch_set_ctrl(base_ctrl(ctx), a.ws.ctrl, ctx->stream), "init control");
     if (st == HMC_OK) st = check_hip(launch_da_init(a, ctx->stream), "init adaptation");
-    if (st == HMC_OK) st = check_hip(launch_bootstrap(a, init_state, ctx->stream), "bootstrap");
+    if (st == HMC_OK) st = bootstrap(ctx, init_state);
     if (st == HMC_OK) st = check_hip(hipStreamSynchronize(ctx->stream), "bootstrap");
     return st;
 }
@@ -430,7 +440,7 @@ hmc_status hmc_set_state(hmc_ctx* ctx, const void* state, const double* step_siz
                                       ctx->stream), "set step size");
     ctx->t = t;
     if (st == HMC_OK) st = check_hip(launch_set_ctrl(base_ctrl(ctx), ctx->a.ws.ctrl, ctx->stream), "set control");
-    if (st == HMC_OK) st = check_hip(launch_bootstrap(ctx->a, state, ctx->stream), "bootstrap");
+    if (st == HMC_OK) st = bootstrap(ctx, state);
     return st;
 }
 
@@ -1021,7 +1031,13 @@ extern "C" hmc_status hmc_nuts_sample_chain(hmc_ctx* ctx, int32_t max_depth, int
         st = check_hip(launch_da_init(ctx->a, ctx->stream), "adaptation init");
     if (st != HMC_OK) return st;
     if ((ctx->form == HMC_FORM_FUSED || ctx->cfg.form == HMC_FORM_AUTO) && nuts_fused_supported(ctx->a)) {
-        // element-wise targets: one persistent launch for all transitions
+        // one persistent launch for all transitions; a state just set starts from the
+        // bootstrap of the persistent kernels, whatever the context's form
+        if (ctx->boot_steps && ctx->t == ctx->t_boot) {
+            st = check_hip(launch_bootstrap(ctx->a, nullptr, false, ctx->stream), "bootstrap");
+            if (st != HMC_OK) return st;
+            ctx->boot_steps = false;
+        }
         st = check_hip(launch_nuts_fused(ctx->a, nw, ad, (uint32_t)ctx->t, total, max_depth, samples, tree_depth,
                                          n_leapfrog, accept_stat, ctx->stream),
                        "nuts persistent");

@@ -124,7 +124,9 @@ int lr32_nsplit(const PlainArgs& a);
 hipError_t launch_lr32_grad(const PlainArgs& a, const float* x, const float* p, int drift, int want_logp, int nsplit,
                             int64_t rows, hipStream_t s);
 hipError_t launch_set_ctrl(const Ctrl& c, Ctrl* dst, hipStream_t s);
-hipError_t launch_bootstrap(const PlainArgs& a, const void* x_src, hipStream_t s);
+// gradient and logp at x_src, copied into ws.x first (NULL: at ws.x); steps: plain-form
+// transitions continue from there, else the fused or persistent kernels
+hipError_t launch_bootstrap(const PlainArgs& a, const void* x_src, bool steps, hipStream_t s);
 hipError_t launch_plain_transition(const PlainArgs& a, bool copy_proposal, hipStream_t s);
 hipError_t launch_da_init(const PlainArgs& a, hipStream_t s);
 hipError_t launch_leapfrog_step(const PlainArgs& a, double ks, hipStream_t s);

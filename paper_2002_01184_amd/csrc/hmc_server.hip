@@ -150,7 +150,7 @@ hipError_t admit(Request* q, void* pool, hipStream_t s) {
     c.tr_lar = q->req.trace.log_accept_ratio;
     c.tr_logp = q->req.trace.target_log_prob;
     if ((e = launch_set_ctrl(c, a.ws.ctrl, s)) != hipSuccess) return e;
-    if ((e = launch_bootstrap(a, q->req.init_state, s)) != hipSuccess) return e;
+    if ((e = launch_bootstrap(a, q->req.init_state, q->form != HMC_FORM_FUSED, s)) != hipSuccess) return e;
     return launch_da_init(a, s);
 }
 

@@ -789,17 +789,12 @@ __global__ __launch_bounds__(64 * DS_NW) void k_dense_step(PlainArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Logistic regression: the gradient partials of each row split (k_logreg_f32.hip,
-// k_logreg_bf16.hip) summed here.
-// ---------------------------------------------------------------------------
-// ---------------------------------------------------------------------------
 // Logistic regression, D <= 32, FP32 gradients: the gradient and log-likelihood
-// partials at a given state (bootstrap, set_state) on v_mfma_f32_16x16x4f32.
-// Runs of these shapes go through the fused and the persistent NUTS kernels,
-// which form their own gradients and only start from this one: it keeps the
-// arithmetic, so that a seed's chains stay the same bit for bit, where the
-// split kernel (k_logreg_f32.hip) rounds differently.  Every leapfrog step of
-// the plain form runs there.
+// partials at a given state (bootstrap, set_state) on v_mfma_f32_16x16x4f32, where
+// the fused or the persistent NUTS kernels continue.  They form their own gradients
+// and only start from this one: it keeps the arithmetic, so that a seed's chains
+// stay the same bit for bit, where the split kernel (k_logreg_f32.hip) rounds
+// differently.  The plain form starts, steps and resumes there.
 // A workgroup (4 waves) owns 64 chains and one split of the rows; wave w runs
 // both contractions for chains c0 + 16 w + i16 over the split's rows, 16 rows
 // at a time:
@@ -1388,7 +1383,7 @@ hipError_t launch_remc_swap(const PlainArgs& a, int64_t K, int64_t M, uint32_t t
 static bool launch_dense_logp(const PlainArgs& a, hipStream_t s);
 
 // gradient (and logp) at ws.x into ws.g / ws.logp
-hipError_t launch_bootstrap(const PlainArgs& a_in, const void* x_src, hipStream_t s) {
+hipError_t launch_bootstrap(const PlainArgs& a_in, const void* x_src, bool steps, hipStream_t s) {
     PlainArgs a = a_in;
     a.timer = nullptr;       // the kernel timer covers transitions only
     const size_t es = a.f64 ? 8 : 4;
@@ -1415,7 +1410,8 @@ hipError_t launch_bootstrap(const PlainArgs& a_in, const void* x_src, hipStream_
             launch_finish(a, (float*)a.ws.x, nullptr, (float*)a.ws.g, lb_grad_nsplit_t(a), 0, 0, 0.0, 0, s);
             (void)launch_lr16_logp(a, (const float*)a.ws.x, s);
         } else {
-            if (a.tg.D <= 32) {
+            // what a transition leaves must be what a resume rebuilds, bit for bit
+            if (a.tg.D <= 32 && !steps) {
                 const int nsplit = launch_lr32_boot(a, s);
                 launch_finish(a, (float*)a.ws.x, nullptr, (float*)a.ws.g, nsplit, 0, 0, 0.0, 1, s);
             } else {

@@ -1,0 +1,51 @@
+"""Accuracy of the FP32 logistic steps against 64 bits over many rows, where
+errors of one sign add up.
+
+The bars count roundings: a term of the log-probability is good to 2^-24 or so,
+and N of them that round independently are off by sqrt(N) 2^-24 together; the
+bars allow four times that.
+"""
+import math
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from gpu_helpers import gpu_available, oracle_target, to_np
+
+pytestmark = pytest.mark.gpu
+
+if not gpu_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import torch  # noqa: E402
+
+from paper_2002_01184_amd import hmc  # noqa: E402
+
+
+def _step(w, L, eps):
+    s = hmc.Sampler(w.kind, w.dim, w.num_chains, L, eps, torch.from_numpy(w.x0).cuda(),
+                    X=torch.from_numpy(w.X_bf16.view(np.int16) if w.X_bf16 is not None else w.X).cuda(),
+                    y=torch.from_numpy(w.y).cuda(), x_bf16=w.X_bf16 is not None, seed=w.seed,
+                    form=hmc.HMC_FORM_PLAIN)
+    s.set_state(torch.from_numpy(np.ascontiguousarray(w.x0)).cuda(), None, 3)
+    g = {k: to_np(v).astype(np.float64) for k, v in s.step(want_proposal=True).items()}
+    s.close()
+    return g
+
+
+@pytest.mark.parametrize("bf16x", [False, True])
+@pytest.mark.parametrize("N,D", [(100000, 5), (60000, 31), (30000, 40)])
+def test_energy_change(N, D, bf16x):
+    # both ends' log-probabilities come from one arithmetic: what they share cancels
+    w = W.logreg(N, D, 64, L=2, step_size=0.001, bf16=bf16x, init=0.1, seed=N + D)
+    g = _step(w, 2, 1.0 / math.sqrt(N * D))
+    tg = oracle_target(w)
+    l0, l1 = (oracle.logp_grad(tg, x)[0] for x in (w.x0.astype(np.float64), g["proposed_state"]))
+    p0 = oracle.momentum(w.seed, w.num_chains, 3, D)
+    dh = l0 - l1 + 0.5 * ((g["proposed_momentum"] ** 2).sum(1) - (p0 ** 2).sum(1))
+    err = math.sqrt(np.mean((g["delta_h"] - dh) ** 2))
+    bar = 4.0 * math.sqrt(2.0 * N) * 2.0 ** -24
+    print(f"{N}x{D} bf16x={bf16x}: energy change off by {err:.1e} (bar {bar:.1e})")
+    assert err <= bar
