@@ -46,6 +46,8 @@
 namespace hmc {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef short bf16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
@@ -73,6 +75,12 @@ __device__ __forceinline__ void split3_pos(float x, uint32_t& h, uint32_t& m, ui
 }
 // the upper halves of a (low 16 bits of the result) and b (high 16 bits)
 __device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+
+// two floats to BF16, rounded to nearest even, a in the low half (v_cvt_pk_bf16_f32)
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    const floatx2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
 
 // e^-|s|, and sigmoid(z) from e = e^-|z|: 1 / (1 + e) for z >= 0, e / (1 + e)
 // below, on the hardware exp2 and reciprocal (1 ulp each).  Correcting the exp2
@@ -327,9 +335,23 @@ __global__ __launch_bounds__(64 * LS_NW, ls_wps(KS)) void k_lr32_step(
             to[k] = (uint32_t)(tr * RB + 16 * ((2 * k + ((l16 & 3) >> 1)) ^ ft) + 8 * (l16 & 1));
     }
 
-    floatx4 gacc[NT];
+    // How G's products are added up.  One after the other into G (X in FP32: 8 a
+    // stage), the small ones are rounded at G's size, and those of a truncated split,
+    // all of their residual's sign, to one side: at 100000 x 2, FP32 X, 500 chains a
+    // gradient was off by 1.0e-6 (2-norm; FP32 MFMA 2.3e-7), at 100000 x 130, 4000
+    // chains by 1.9e-6 (5.7e-7).  So the residuals are split by rounding, the partials
+    // summed by eights, and G rounds once a stage: now 6.7e-8 and 1.2e-7.  Up to 128
+    // dims the products besides the leading one have accumulators of their own (no
+    // slower, but for 33 to 64 dims of FP32 X, where they would cost a wave: 98.5 ->
+    // 103.5 us a step at 20000 x 60, 2048 chains); elsewhere a stage's products meet in
+    // a sum that starts at zero (20000 x 150, FP32 X, 1000 chains 115 -> 117 us; beyond
+    // 256 dims fewer spills: 512 dims 458 -> 433, BF16 X 315 -> 212).  BF16 X, whose
+    // three products lose less, goes without at 129 to 256 dims (256 dims 199 -> 206):
+    // 3.7e-7 at 100000 x 130.
+    constexpr bool GC = KS <= 4 && !(XT == 3 && KS == 2), GS = !GC && (XT == 3 || KS > 8);
+    floatx4 gacc[NT], gcor[GC ? NT : 1];
 #pragma unroll
-    for (int n = 0; n < NT; ++n) gacc[n] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int n = 0; n < NT; ++n) gacc[n] = gcor[GC ? n : 0] = floatx4{0.f, 0.f, 0.f, 0.f};
     double lp = 0.0;
 
     if (nst > 0) {
@@ -400,9 +422,9 @@ __global__ __launch_bounds__(64 * LS_NW, ls_wps(KS)) void k_lr32_step(
             }
             if (RD == 2) read_t(0, xf[0]);
             const uint32_t* yl = (const uint32_t*)(buf + XT * PLANE) + 4 * g;
-            // residuals y - sigmoid(s) = y ? sigmoid(-s) : -sigmoid(s), split into three
-            // BF16 terms; rows past the split are zero in X and add nothing to G
-            uint32_t rh[8], rm[8], rl[8];
+            // residuals y - sigmoid(s) = y ? sigmoid(-s) : -sigmoid(s), split into three BF16
+            // terms by rounding; rows past the split are zero in X and add nothing to G
+            float rf[8];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const uint4 yw = *(const uint4*)(yl + 16 * h);
@@ -414,11 +436,7 @@ __global__ __launch_bounds__(64 * LS_NW, ls_wps(KS)) void k_lr32_step(
                     const float e = exp_neg_abs(s);
                     const float sg = sigmoid_from(z, e);
                     const float r = yv[v] ? sg : -sg;
-                    const uint32_t u = __float_as_uint(r);
-                    rh[4 * h + v] = u;
-                    const float r1 = r - __uint_as_float(u & 0xffff0000u);
-                    rm[4 * h + v] = __float_as_uint(r1);
-                    rl[4 * h + v] = __float_as_uint(r1 - __uint_as_float(__float_as_uint(r1) & 0xffff0000u));
+                    rf[4 * h + v] = r;
                     if constexpr (LOGP) {
                         const int64_t row = r_begin + (int64_t)st * LS_RS + 16 * h + 4 * g + v;
                         if (row < r_end) lp -= (double)(fmaxf(z, 0.f) + log1pf(e));
@@ -426,13 +444,20 @@ __global__ __launch_bounds__(64 * LS_NW, ls_wps(KS)) void k_lr32_step(
                 }
             }
             bf16x8 rb[3];
-            auto packed = [](const uint32_t (&v)[8]) {
-                return __builtin_bit_cast(bf16x8, make_uint4(pack_hi(v[0], v[1]), pack_hi(v[2], v[3]),
-                                                             pack_hi(v[4], v[5]), pack_hi(v[6], v[7])));
-            };
-            rb[0] = packed(rh);
-            rb[1] = packed(rm);
-            rb[2] = packed(rl);
+            uint32_t rw[3][4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                float a0 = rf[2 * j], a1 = rf[2 * j + 1];
+#pragma unroll
+                for (int t = 0; t < 3; ++t) {
+                    rw[t][j] = pack_bf16(a0, a1);
+                    a0 -= __uint_as_float(rw[t][j] << 16);
+                    a1 -= __uint_as_float(rw[t][j] & 0xffff0000u);
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+                rb[t] = __builtin_bit_cast(bf16x8, make_uint4(rw[t][0], rw[t][1], rw[t][2], rw[t][3]));
             // G += X^T R, two dim tiles at a time
             if (RD == 2) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
@@ -440,13 +465,24 @@ __global__ __launch_bounds__(64 * LS_NW, ls_wps(KS)) void k_lr32_step(
                 if (RD == 1) read_t(n0, xf[0]);
                 else if (n0 + 2 < NT) read_t(n0 + 2, xf[(n0 / 2 + 1) % RD]);
                 const bf16x8(&xt)[2][XT] = xf[(n0 / 2) % RD];
+                floatx4 gs[2];
+                if (GS)
+#pragma unroll
+                    for (int n = 0; n < 2; ++n) gs[n] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int i = 0; i < (XT == 1 ? 3 : 8); ++i) {
                     constexpr int XI[8] = {2, 1, 2, 0, 1, 1, 0, 0}, TI[8] = {1, 2, 0, 2, 1, 0, 1, 0};
                     const int xi = XT == 1 ? 0 : XI[i], ti = XT == 1 ? 2 - i : TI[i];
 #pragma unroll
-                    for (int n = 0; n < 2; ++n) LS_MFMA(xt[n][xi], rb[ti], gacc[n0 + n]);
+                    for (int n = 0; n < 2; ++n) {
+                        if (GS) LS_MFMA(xt[n][xi], rb[ti], gs[n]);
+                        else if (GC && xi + ti > 0) LS_MFMA(xt[n][xi], rb[ti], gcor[GC ? n0 + n : 0]);
+                        else LS_MFMA(xt[n][xi], rb[ti], gacc[n0 + n]);
+                    }
                 }
+                if (GS)
+#pragma unroll
+                    for (int n = 0; n < 2; ++n) gacc[n0 + n] += gs[n];
                 if (RD == 2) __builtin_amdgcn_sched_barrier(0);
             }
 #undef LS_MFMA
@@ -469,6 +505,7 @@ __global__ __launch_bounds__(64 * LS_NW, ls_wps(KS)) void k_lr32_step(
     const bool v4 = (D & 3) == 0;
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
+        if (GC) gacc[n] += gcor[GC ? n : 0];
         const int d = 16 * n + 4 * g;
         if (v4) {
             if (d < D) *(floatx4*)(pg + d) = gacc[n];

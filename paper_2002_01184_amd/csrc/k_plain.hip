@@ -1044,9 +1044,11 @@ __global__ __launch_bounds__(256) void k_lr32_boot(PlainArgs a, const float* __r
     if (cv && q == 0) a.ws.part_lp[(int64_t)split * C + c] = lp;
 }
 
-// Sum of p[s * stride], s = 0 .. n - 1, in that order, with U loads in flight (a
-// load per add waits for each: 64 splits would cost 64 L2 latencies).
-template <int U, typename T>
+// Sum of p[s * stride], s = 0 .. n - 1, with U loads in flight (a load per add
+// waits for each: 64 splits would cost 64 L2 latencies): in that order, or (EIGHTS)
+// eight at a time, whose sums are added in order -- fewer roundings at the size of
+// the whole sum.
+template <int U, bool EIGHTS, typename T>
 __device__ __forceinline__ T split_sum(const T* __restrict__ p, int64_t stride, int n) {
     T sum = T{};
     int s0 = 0;
@@ -1056,15 +1058,23 @@ __device__ __forceinline__ T split_sum(const T* __restrict__ p, int64_t stride, 
 #pragma unroll
             for (int k = 0; k < U; ++k) v[k] = p[(int64_t)(s0 + k) * stride];
 #pragma unroll
-            for (int k = 0; k < U; ++k) sum += v[k];
+            for (int k = 0; k < U; k += EIGHTS ? 8 : 1) {
+                T t = v[k];
+                if constexpr (EIGHTS)
+#pragma unroll
+                    for (int j = 1; j < 8; ++j) t += v[k + j];
+                sum += t;
+            }
         }
     for (; s0 < n; s0 += 8) {
         T v[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) v[k] = p[(int64_t)(s0 + k < n ? s0 + k : n - 1) * stride];
+        T t = EIGHTS ? v[0] : sum;
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
-            if (s0 + k < n) sum += v[k];
+        for (int k = EIGHTS ? 1 : 0; k < 8; ++k)
+            if (s0 + k < n) t += v[k];
+        sum = EIGHTS ? sum + t : t;
     }
     return sum;
 }
@@ -1074,7 +1084,7 @@ __device__ __forceinline__ T split_sum(const T* __restrict__ p, int64_t stride, 
 // thread: 1, or 4 by 16-byte accesses (D a multiple of 4) where the elements fill
 // the chip anyway and the launch is bound by the partials' bytes (8192 x 256, 8
 // splits: 17.0 us; 23.9 by single elements with 32 loads in flight).
-template <int V>
+template <int V, bool EIGHTS>
 __device__ __forceinline__ void finish_body(const PlainArgs& a, float* __restrict__ xd, float* __restrict__ pd,
                                             float* __restrict__ gd, int nsplit, int drift, int kick,
                                             double kick_scale, int want_logp, int64_t blk, int64_t nblk) {
@@ -1087,7 +1097,7 @@ __device__ __forceinline__ void finish_body(const PlainArgs& a, float* __restric
         vec x = *(const vec*)(xd + i);
         const vec p = (drift || kick) ? *(const vec*)(pd + i) : vec{};
         const double eps = a.ws.eps[c], bt = a.ws.beta ? a.ws.beta[c] : 1.0;
-        const vec gsum = split_sum<V == 1 ? 32 : 8>((const vec*)(a.ws.part_g + i), n / V, nsplit);
+        const vec gsum = split_sum<V == 1 ? 32 : 8, EIGHTS>((const vec*)(a.ws.part_g + i), n / V, nsplit);
         vec pn, gv;
 #pragma unroll
         for (int j = 0; j < V; ++j) {
@@ -1099,15 +1109,15 @@ __device__ __forceinline__ void finish_body(const PlainArgs& a, float* __restric
         if (drift) *(vec*)(xd + i) = x;
         if (kick) *(vec*)(pd + i) = pn;
         if (gd) *(vec*)(gd + i) = gv;
-        if (want_logp && i - c * D == 0) a.ws.lpq[c] = split_sum<32>(a.ws.part_lp + c, C, nsplit);
+        if (want_logp && i - c * D == 0) a.ws.lpq[c] = split_sum<32, false>(a.ws.part_lp + c, C, nsplit);
     }
 }
 
-template <int V>
+template <int V, bool EIGHTS>
 __global__ __launch_bounds__(256) void k_logreg_finish(PlainArgs a, float* __restrict__ xd, float* __restrict__ pd,
                                                        float* __restrict__ gd, int nsplit, int drift, int kick,
                                                        double kick_scale, int want_logp) {
-    finish_body<V>(a, xd, pd, gd, nsplit, drift, kick, kick_scale, want_logp, blockIdx.x, gridDim.x);
+    finish_body<V, EIGHTS>(a, xd, pd, gd, nsplit, drift, kick, kick_scale, want_logp, blockIdx.x, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1138,7 +1148,7 @@ __global__ __launch_bounds__(256) void k_finish_multi(const Lr16Job* __restrict_
     const int j = lr16_job_of(jobs, njobs, LR16_KIND_FINISH, blockIdx.x, &lb);
     if (j < 0) return;
     const PlainArgs a = jobs[j].a;
-    finish_body<1>(a, (float*)a.ws.xq, (float*)a.ws.pq, last ? (float*)a.ws.gq : nullptr, jobs[j].nsplit_g, 1, 1,
+    finish_body<1, false>(a, (float*)a.ws.xq, (float*)a.ws.pq, last ? (float*)a.ws.gq : nullptr, jobs[j].nsplit_g, 1, 1,
                 last ? 0.5 : 1.0, 0, lb, jobs[j].nblk[LR16_KIND_FINISH]);
 }
 
@@ -1234,15 +1244,16 @@ static int launch_lr32_boot(const PlainArgs& a, hipStream_t s) {
     return nsplit;
 }
 
+template <bool EIGHTS = false>
 static void launch_finish(const PlainArgs& a, float* x, float* p, float* gd, int nsplit, int drift, int kick,
                           double ks, int want_logp, hipStream_t s) {
     const int64_t n = a.C * a.tg.D;
     if (a.tg.D % 4 == 0 && n >= (1 << 19))
-        hipLaunchKernelGGL(k_logreg_finish<4>, elem_grid(n / 4), dim3(256), 0, s, a, x, p, gd, nsplit, drift, kick, ks,
-                           want_logp);
+        hipLaunchKernelGGL((k_logreg_finish<4, EIGHTS>), elem_grid(n / 4), dim3(256), 0, s, a, x, p, gd, nsplit, drift,
+                           kick, ks, want_logp);
     else
-        hipLaunchKernelGGL(k_logreg_finish<1>, elem_grid(n), dim3(256), 0, s, a, x, p, gd, nsplit, drift, kick, ks,
-                           want_logp);
+        hipLaunchKernelGGL((k_logreg_finish<1, EIGHTS>), elem_grid(n), dim3(256), 0, s, a, x, p, gd, nsplit, drift, kick,
+                           ks, want_logp);
 }
 
 // One FP32 gradient evaluation of logistic regression at x (drifted in place
@@ -1257,7 +1268,7 @@ static hipError_t launch_logreg(const PlainArgs& a, float* x, float* p, float* g
     const hipError_t e = launch_lr32_grad(a, x, p, drift, want_logp, nsplit, rows, s);
     timer_end(a, s, "k_lr32_step");
     if (e != hipSuccess) return e;
-    launch_finish(a, x, p, gd, nsplit, drift, kick, ks, want_logp, s);
+    launch_finish<true>(a, x, p, gd, nsplit, drift, kick, ks, want_logp, s);
     return hipGetLastError();
 }
 

@@ -49,3 +49,24 @@ def test_energy_change(N, D, bf16x):
     bar = 4.0 * math.sqrt(2.0 * N) * 2.0 ** -24
     print(f"{N}x{D} bf16x={bf16x}: energy change off by {err:.1e} (bar {bar:.1e})")
     assert err <= bar
+
+
+@pytest.mark.parametrize("bf16x", [False, True])
+@pytest.mark.parametrize("N,D,C,splits", [(100000, 2, 64, 64), (100000, 31, 64, 64), (60000, 100, 64, 64),
+                                          (100000, 130, 4000, 8), (30000, 300, 64, 64)])
+def test_gradient(N, D, C, splits, bf16x):
+    # A split's sums round once a stage of 32 rows, independently, 2^-24 of a sum that is
+    # half grown on average; four more roundings on the way into the momentum.  The chains
+    # start far enough from the mode that the rows' terms do not cancel.
+    w = W.logreg(N, D, C, L=1, step_size=0.001, bf16=bf16x, init=0.1, seed=N + D)
+    eps = 20.0 / math.sqrt(N)
+    g = _step(w, 1, eps)
+    some = np.arange(0, C, max(1, C // 8))
+    tg = oracle_target(w)
+    g0, g1 = (oracle.logp_grad(tg, x[some])[1] for x in (w.x0.astype(np.float64), g["proposed_state"]))
+    kick = 0.5 * eps * (g0 + g1)
+    err = np.linalg.norm(g["proposed_momentum"][some] - oracle.momentum(w.seed, C, 3, D)[some] - kick)
+    err /= np.linalg.norm(kick)
+    bar = (0.5 * math.sqrt(math.ceil(N / splits / 32)) + 4.0) * 2.0 ** -24
+    print(f"{N}x{D} C={C} bf16x={bf16x}: gradient off by {err:.1e} (bar {bar:.1e})")
+    assert err <= bar
