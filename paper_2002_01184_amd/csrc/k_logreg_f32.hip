@@ -82,14 +82,20 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// e^-|s|, and sigmoid(z) from e = e^-|z|: 1 / (1 + e) for z >= 0, e / (1 + e)
-// below, on the hardware exp2 and reciprocal (1 ulp each).  Correcting the exp2
-// for its argument's rounding and the reciprocal by a Newton step changed the
-// gradient's error against 64 bits in the third digit only (S carries more), and
-// cost 2 to 6% of the step.
+// e^-|s| on the hardware exp2 (1 ulp).  ACC: corrected to first order for the
+// rounding of its argument (relative |s| 7e-8) and of log2 e (one-sided, |s| 1.3e-8),
+// which the rows of a log-probability or of a narrow gradient add up: 100000 x 5,
+// 500 chains, the log-probability off by 1.7e-4 without, 2.0e-5 with it (6.5e-5 with
+// expf).  A Newton step on the reciprocal below changed nothing.
+template <bool ACC>
 __device__ __forceinline__ float exp_neg_abs(float s) {
-    return __builtin_amdgcn_exp2f(-1.4426950408889634f * fabsf(s));
+    const float c = -1.4426950408889634f, as = fabsf(s);       // -log2 e, rounded; off by -1.93e-8
+    const float t = c * as, e = __builtin_amdgcn_exp2f(t);
+    if constexpr (!ACC) return e;
+    const float d = fmaf(-1.92596303e-8f, as, fmaf(c, as, -t));
+    return fmaf(0.69314718055994531f * e, t > -200.f ? d : 0.f, e);    // s infinite: d = NaN, e = 0
 }
+// sigmoid(z) from e = e^-|z|: 1 / (1 + e) for z >= 0, e / (1 + e) below
 __device__ __forceinline__ float sigmoid_from(float z, float e) {
     const float r = __builtin_amdgcn_rcpf(1.0f + e);
     return z >= 0.f ? r : e * r;
@@ -224,8 +230,8 @@ struct LsStage {
 };
 
 // LOGP: the log-likelihood of every chain as well (the bootstrap, the last
-// step of a trajectory and the NUTS leaves).
-template <int XT, int KS, bool LOGP>
+// step of a trajectory and the NUTS leaves).  ACC: the corrected exponential.
+template <int XT, int KS, bool LOGP, bool ACC>
 __global__ __launch_bounds__(64 * LS_NW, ls_wps(KS)) void k_lr32_step(
     PlainArgs a, const float* __restrict__ xsrc, const float* __restrict__ psrc, int drift, int ntile, int nsplit,
     int64_t rows_per_split) {
@@ -433,7 +439,7 @@ __global__ __launch_bounds__(64 * LS_NW, ls_wps(KS)) void k_lr32_step(
                 for (int v = 0; v < 4; ++v) {
                     const float s = sh[h][v] + sl[h][v];
                     const float z = yv[v] ? -s : s;
-                    const float e = exp_neg_abs(s);
+                    const float e = exp_neg_abs<ACC>(s);
                     const float sg = sigmoid_from(z, e);
                     const float r = yv[v] ? sg : -sg;
                     rf[4 * h + v] = r;
@@ -521,12 +527,12 @@ __global__ __launch_bounds__(64 * LS_NW, ls_wps(KS)) void k_lr32_step(
 // ---------------------------------------------------------------------------
 // Launcher
 // ---------------------------------------------------------------------------
-template <int XT, int KS, bool LOGP>
+template <int XT, int KS, bool LOGP, bool ACC>
 static hipError_t ls_launch(const PlainArgs& a, const float* x, const float* p, int drift, int nsplit, int64_t rows,
                             hipStream_t s) {
     using P = LsShape<XT, KS>;
     const int ntile = (int)((a.C + 16 * LS_NW - 1) / (16 * LS_NW));
-    auto kern = k_lr32_step<XT, KS, LOGP>;
+    auto kern = k_lr32_step<XT, KS, LOGP, ACC>;
     if (P::LDS > 65536)
         (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, P::LDS);
     hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)ntile * nsplit)), dim3(64 * LS_NW), P::LDS, s, a, x, p, drift,
@@ -538,9 +544,15 @@ template <int XT>
 static hipError_t ls_ks(const PlainArgs& a, const float* x, const float* p, int drift, int want_logp, int nsplit,
                         int64_t rows, hipStream_t s) {
     const int ks = (int)((a.tg.D + 31) / 32);
+    // Gradients of up to 16 dims take the corrected exponential too.  Near the mode,
+    // where the rows' terms cancel, what is left of the link's error beside FP32 MFMA's
+    // whole error (100000 rows, FP32 X, 500 chains, without and with): 2 dims 1.18,
+    // 0.32; 8 dims 0.55, 0.30; 16 dims 0.38, 0.37; 32 dims 0.40, 0.48.  It costs 50000 x
+    // 8 (2048 chains) 136 -> 150 us a step and would cost 10000 x 25 28.5 -> 29.5.
+    if (!want_logp && a.tg.D <= 16) return ls_launch<XT, 1, false, true>(a, x, p, drift, nsplit, rows, s);
 #define LS_KS(K) \
-    if (ks <= K) return want_logp ? ls_launch<XT, K, true>(a, x, p, drift, nsplit, rows, s) \
-                              : ls_launch<XT, K, false>(a, x, p, drift, nsplit, rows, s);
+    if (ks <= K) return want_logp ? ls_launch<XT, K, true, true>(a, x, p, drift, nsplit, rows, s) \
+                              : ls_launch<XT, K, false, false>(a, x, p, drift, nsplit, rows, s);
     LS_KS(1) LS_KS(2) LS_KS(3) LS_KS(4) LS_KS(5) LS_KS(6) LS_KS(7) LS_KS(8) LS_KS(10) LS_KS(12) LS_KS(14) LS_KS(16)
 #undef LS_KS
     return hipErrorInvalidValue;

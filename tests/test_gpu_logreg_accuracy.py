@@ -70,3 +70,38 @@ def test_gradient(N, D, C, splits, bf16x):
     bar = (0.5 * math.sqrt(math.ceil(N / splits / 32)) + 4.0) * 2.0 ** -24
     print(f"{N}x{D} C={C} bf16x={bf16x}: gradient off by {err:.1e} (bar {bar:.1e})")
     assert err <= bar
+
+
+@pytest.mark.parametrize("bf16x", [False, True])
+@pytest.mark.parametrize("N,D", [(100000, 2), (100000, 5), (60000, 31), (60000, 100)])
+def test_log_probability(N, D, bf16x):
+    w = W.logreg(N, D, 64, L=1, step_size=0.001, bf16=bf16x, init=0.1, seed=N + D)
+    g = _step(w, 1, 1e-3 / math.sqrt(N * D))                 # every proposal is accepted
+    assert g["is_accepted"].all()
+    lp = oracle.logp_grad(oracle_target(w), g["proposed_state"])[0]
+    err = math.sqrt(np.mean((g["target_log_prob"] - lp) ** 2))
+    bar = 4.0 * math.sqrt(N) * 2.0 ** -24
+    print(f"{N}x{D} bf16x={bf16x}: log-probability off by {err:.1e} (bar {bar:.1e})")
+    assert err <= bar
+
+
+@pytest.mark.parametrize("D", [3, 5, 16])
+def test_gradient_near_the_mode(D):
+    # There the rows' terms, N of about 0.3, cancel to sqrt(N) of them, and an error of one
+    # sign in every term stands out in the mean over chains.  Terms good to 2^-24 that
+    # round either way leave about 2^-24 of the gradient; the bar allows twice that.  The
+    # middle gradient of two steps is formed without the log-probability; its position is
+    # the end of one step.
+    N, C = 60000, 192
+    w = W.logreg(N, D, C, L=2, step_size=0.001, init=1.0 / math.sqrt(N), seed=N + D)
+    eps = 1.0 / math.sqrt(N)
+    one, two = _step(w, 1, eps), _step(w, 2, eps)
+    tg = oracle_target(w)
+    g0, g1, g2 = (oracle.logp_grad(tg, x)[1] for x in (w.x0.astype(np.float64), one["proposed_state"],
+                                                       two["proposed_state"]))
+    kick = 0.5 * g0 + g1 + 0.5 * g2
+    err = (two["proposed_momentum"] - oracle.momentum(w.seed, C, 3, D)) / eps - kick
+    err = np.linalg.norm(err.mean(0)) / math.sqrt(np.mean((kick ** 2).sum(1)))
+    bar = 2.0 * 2.0 ** -24
+    print(f"{N}x{D}: mean gradient off by {err:.1e} (bar {bar:.1e})")
+    assert err <= bar
