@@ -63,13 +63,15 @@ __device__ __forceinline__ void split3(float x, uint32_t& h, uint32_t& m, uint32
     m = __float_as_uint(r1) & 0xffff0000u;
     l = __float_as_uint(r1 - __uint_as_float(m));
 }
-// The same for a chain's position: a value that is not finite (a trajectory that
-// diverged) keeps its leading term only, so that an infinite position meets X as
-// it would in FP32.
+// The same for a chain's position.  An infinite one (a trajectory that diverged)
+// enters as the largest BF16 number: times an entry of X it gives an infinite logit,
+// or one whose sigmoid is 0 or 1 as well, and times the zeros that stand for rows past
+// a split's end and for the smaller terms of X it gives zero and no NaN, so that the
+// other coordinates' gradients stay as finite as in FP32.  NaN stays in the smaller terms.
 __device__ __forceinline__ void split3_pos(float x, uint32_t& h, uint32_t& m, uint32_t& l) {
-    h = x == x ? __float_as_uint(x) & 0xffff0000u : 0x7fc00000u;
-    const float d = x - __uint_as_float(h);
-    const float r1 = fabsf(x) < __builtin_inff() ? d : 0.f;
+    const uint32_t b = __float_as_uint(x);
+    h = min(b & 0x7fff0000u, 0x7f7f0000u) | (b & 0x80000000u);
+    const float r1 = (b & 0x7fffffffu) == 0x7f800000u ? 0.f : x - __uint_as_float(h);
     m = __float_as_uint(r1) & 0xffff0000u;
     l = __float_as_uint(r1 - __uint_as_float(m));
 }
