@@ -587,7 +587,7 @@ hmc_status hmc_sample_chain_noalloc(const hmc_target* target, const hmc_config* 
 // ---------------------------------------------------------------------------
 // Autotuner: times the launch configurations that apply to this context with
 // HIP events on its stream, restores the chain state after every trial, and
-// keeps the fastest.  Choices are cached per (target family, D, log2 N,
+// keeps the fastest.  Choices are cached per (version, target family, D, log2 N,
 // log2 C, dtypes, L, requested form) in memory and, when HMC_AUTOTUNE_CACHE
 // names a file, on disk (one "key form lr_nsplit lr16_nsplit elem_gmult" line
 // per entry).
@@ -610,9 +610,13 @@ int ilog2(int64_t v) {
     return r;
 }
 
+// Part of every key: raised when a kernel that the choices are about is replaced,
+// so that a file's choices for the old one are passed over.
+constexpr char kTuneVersion[] = "v2";
+
 std::string tune_key(const hmc_ctx* ctx) {
     std::ostringstream k;
-    k << ctx->a.tg.kind << ":" << ctx->a.tg.D << ":" << ilog2(ctx->a.tg.N + 1) << ":" << ilog2(ctx->a.C) << ":"
+    k << kTuneVersion << ":" << ctx->a.tg.kind << ":" << ctx->a.tg.D << ":" << ilog2(ctx->a.tg.N + 1) << ":" << ilog2(ctx->a.C) << ":"
       << ctx->cfg.state_dtype << ":" << ctx->cfg.grad_dtype << ":" << ctx->a.L << ":" << ctx->cfg.form;
     return k.str();
 }
@@ -724,12 +728,21 @@ extern "C" hmc_status hmc_autotune(hmc_ctx* ctx, int32_t trial_transitions, char
                 cands.push_back(c);
             }
         } else if (f != HMC_FORM_FUSED && ctx->a.tg.kind == HMC_TGT_LOGREG) {
-            const int64_t d = logreg_nsplit(ctx->a.tg.N, ctx->a.C);
-            for (int64_t s : {d / 2, d, 2 * d})
-                if (s >= 1 && s <= 64) {
-                    c.tune.lr_nsplit = (int32_t)s;
-                    cands.push_back(c);
-                }
+            // the step's own choice (0), and half and twice as many splits, in the multiples
+            // of 8 that keep a split's tiles on one XCD
+            PlainArgs untuned = ctx->a;
+            untuned.tune = Tune{0, 0, 0};
+            const int64_t d = lr32_nsplit(untuned), cap = logreg_nsplit_cap(ctx->a.tg.N, ctx->a.C);
+            int64_t last = d;
+            cands.push_back(c);
+            for (int64_t s : {d / 2, 2 * d}) {
+                if (s > cap) s = cap;
+                if (s > 8) s = s / 8 * 8;
+                if (s < 1 || s == d || s == last) continue;
+                last = s;
+                c.tune.lr_nsplit = (int32_t)s;
+                cands.push_back(c);
+            }
         } else {
             cands.push_back(c);
         }
