@@ -692,7 +692,8 @@ extern "C" hmc_status hmc_autotune(hmc_ctx* ctx, int32_t trial_transitions, char
         std::lock_guard<std::mutex> lk(g_tune_mu);
         load_cache_locked();
         auto it = g_tune_cache.find(key);
-        if (it != g_tune_cache.end()) {
+        // one bucket of rows may hold contexts on both sides of the fused kernel's limit
+        if (it != g_tune_cache.end() && (it->second.form != HMC_FORM_FUSED || fused_supported(ctx->a))) {
             ctx->form = it->second.form;
             ctx->a.tune = it->second.tune;
             drop_graph(ctx);

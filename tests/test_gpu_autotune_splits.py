@@ -46,3 +46,16 @@ def test_choices_for_replaced_kernels_are_passed_over(tmp_path):
                                     capture_output=True, text=True).stdout for _ in range(2))
     assert "REPORT form=1" in first and "cached" not in first
     assert "REPORT cached" in second
+
+
+def test_choice_of_the_fused_form_is_not_taken_where_it_does_not_fit(tmp_path):
+    # 1024 and 1500 rows share a key; the fused logistic kernel ends at 1024
+    code = ("import workloads as W; from paper_2002_01184_amd import hmc; "
+            "s = hmc.sampler_for(W.logreg(1500, 25, 64, L=2, step_size=0.01, seed=1)); "
+            "s.autotune(1); s.sample_chain(2, 0); print('FORM', s.form); s.close()")
+    path = tmp_path / "choices"
+    path.write_text("v2:3:25:10:6:1:1:2:0 2 0 0 0\n")
+    env = dict(os.environ, HMC_AUTOTUNE_CACHE=str(path), PYTHONPATH=ROOT)
+    out = subprocess.run([sys.executable, "-c", code], cwd=ROOT, env=env, timeout=60, capture_output=True, text=True)
+    assert out.returncode == 0, out.stderr
+    assert "FORM plain" in out.stdout or "FORM graph" in out.stdout
