@@ -169,13 +169,21 @@ __global__ __launch_bounds__(256) void k_nuts_dir(PlainArgs a, NutsWs n, uint32_
 }
 
 // first half kick of a leaf's leapfrog step: p += (v eps / 2) g
-template <typename T>
+// DRIFT (the dense Gaussian, whose gradient kernel reads a drifted position): x +=
+// eps p as well (a launch of its own: 1671 us for two transitions up to depth 5 at D =
+// 8, 1000 chains; here 1469).
+template <typename T, bool DRIFT>
 __global__ __launch_bounds__(256) void k_nuts_halfkick(PlainArgs a, NutsWs n) {
     const int64_t D = a.tg.D, tot = a.C * D;
     T* pq = (T*)a.ws.pq;
     const T* gq = (const T*)a.ws.gq;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < tot; i += (int64_t)gridDim.x * blockDim.x)
-        pq[i] = pq[i] + (T)(0.5 * n.seps[i / D]) * gq[i];
+    T* xq = (T*)a.ws.xq;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < tot; i += (int64_t)gridDim.x * blockDim.x) {
+        const double e = n.seps[i / D];
+        const T p = pq[i] + (T)(0.5 * e) * gq[i];
+        pq[i] = p;
+        if (DRIFT) xq[i] = fma((T)e, p, xq[i]);
+    }
 }
 
 // leaf i of doubling j: its energy, then the merges of the subtrees that end here
@@ -1750,8 +1758,10 @@ hipError_t launch_nuts_dir(const PlainArgs& a, const NutsWs& n, uint32_t t, int3
 hipError_t launch_nuts_halfkick(const PlainArgs& a, const NutsWs& n, hipStream_t s) {
     const int64_t tot = a.C * a.tg.D;
     const dim3 grid((unsigned)((tot + 255) / 256 < 65536 ? (tot + 255) / 256 : 65536));
-    if (a.f64) hipLaunchKernelGGL(k_nuts_halfkick<double>, grid, dim3(256), 0, s, a, n);
-    else hipLaunchKernelGGL(k_nuts_halfkick<float>, grid, dim3(256), 0, s, a, n);
+    if (a.tg.kind == HMC_TGT_GAUSS_DENSE)
+        hipLaunchKernelGGL((k_nuts_halfkick<float, true>), grid, dim3(256), 0, s, a, n);
+    else if (a.f64) hipLaunchKernelGGL((k_nuts_halfkick<double, false>), grid, dim3(256), 0, s, a, n);
+    else hipLaunchKernelGGL((k_nuts_halfkick<float, false>), grid, dim3(256), 0, s, a, n);
     return hipGetLastError();
 }
 

@@ -94,18 +94,6 @@ __global__ __launch_bounds__(256) void k_begin_drift(PlainArgs a, float* drift_t
     begin_body<float, 64>(a, blockIdx.x, drift_to);
 }
 
-// x += eps p on the trajectory buffers (the NUTS leaves of the dense Gaussian)
-__global__ __launch_bounds__(256) void k_drift(PlainArgs a) {
-    const int64_t D = a.tg.D, n = a.C * D;
-    float* x = (float*)a.ws.xq;
-    const float* p = (const float*)a.ws.pq;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t c = i / D;
-        const double e = a.ws.eps[c];
-        x[i] = fmaf(a.ws.scale ? (float)(e * a.ws.scale[i - c * D]) : (float)e, p[i], x[i]);
-    }
-}
-
 // logp at (x, g) from the closed form that remains after the gradient kernel:
 // Gaussians 1/2 x.g; logistic regression -|x|^2/(2 s^2) + the data part in lpq.
 template <typename T, int G>
@@ -1439,7 +1427,8 @@ hipError_t launch_bootstrap(const PlainArgs& a_in, const void* x_src, bool steps
 
 // One leapfrog drift + gradient + kick (scale ks) on the trajectory buffers
 // (xq, pq, gq), the gradient always written to gq and, for logistic
-// regression, the data part of logp to lpq.  Used by the NUTS leaves.
+// regression, the data part of logp to lpq.  Used by the NUTS leaves; the dense
+// Gaussian's drift is made by their half kick before it.
 hipError_t launch_leapfrog_step(const PlainArgs& a, double ks, hipStream_t s) {
     switch (a.tg.kind) {
     case HMC_TGT_STD_NORMAL:
@@ -1452,7 +1441,7 @@ hipError_t launch_leapfrog_step(const PlainArgs& a, double ks, hipStream_t s) {
                                (const float*)a.ws.xq, (float*)a.ws.xq, (float*)a.ws.pq, (float*)a.ws.gq, 3, ks);
         break;
     case HMC_TGT_GAUSS_DENSE:
-        hipLaunchKernelGGL(k_drift, elem_grid(a.C * a.tg.D), dim3(256), 0, s, a);
+        // drifted by the half kick before it
         (void)launch_dense_grad(a, (const float*)a.ws.xq, nullptr, (float*)a.ws.pq, (float*)a.ws.gq, ks, s);
         break;
     case HMC_TGT_LOGREG:
