@@ -225,6 +225,10 @@ void lr16_job_shape(const PlainArgs& a, Lr16Job* j);
 // One launch of kernel kind k (GRAD, LOGP or LPSUM) over all jobs.
 hipError_t launch_lr16_kind_multi(int kind, int64_t D, const Lr16Job* jobs_dev, int njobs, int64_t blocks,
                                   hipStream_t s);
+// What a request's gradient takes by itself, in 1/1024 of a round of the many-chain
+// kernel over as many rows (fewer where the few-chain kernel runs it), and the
+// 32-row sub-tiles of its longest row split.
+int64_t lr16_alone_cost(const PlainArgs& a, int64_t* subs);
 // Block ranges of every job (fills the shapes); false if a grid would exceed 2^31 blocks.
 bool lr16_layout(Lr16Job* jobs, int njobs);
 // One transition of every job (host copy of the table for the grid sizes, device copy for the kernels).

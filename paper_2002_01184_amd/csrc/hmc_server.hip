@@ -162,6 +162,33 @@ bool lr16_fills_gpu(const PlainArgs& a) {
     return j.nblk[LR16_KIND_GRAD] >= 256;
 }
 
+// Whether the members of one class of BF16 logistic requests share launches.  Shared
+// launches run the many-chain kernel, whose round of 256 workgroups takes as long for
+// one as for all; alone, few chains run on a kernel of their own in a fraction of that
+// (lr16_alone_cost), on as many streams as there are.  So up to kStreams members run
+// side by side where that is less work.  us a transition (L = 10) shared and apart,
+// for 2 / 3 / 4 members: 20011 x 150, 200 chains 1395, 458 / 1409, 553 / 1417, 732;
+// 1000 chains 1479, 901 / 1510, 1294 / 1539, 1706; 100000 x 256, 1000 chains 6240,
+// 5070 / 6381, 7634 / 6476, 10129; 2000 chains 6372, 6841; eight of 20011 x 150, 200
+// chains 1459, 1338.  Splits of few rows are bound by the host's launches, which
+// members share: 2000 x 50, 64 chains 198, 195 / 206, 226 / 210, 387.
+bool lr16_share(const std::vector<Request*>& m) {
+    if (m.size() < 2) return false;
+    if (m.size() > (size_t)kStreams) return true;
+    int64_t most = 0, blocks = 0, cost[kStreams], subs[kStreams];
+    for (size_t i = 0; i < m.size(); ++i) {
+        Lr16Job j;
+        lr16_job_shape(m[i]->a, &j);
+        blocks += j.nblk[LR16_KIND_GRAD];
+        cost[i] = lr16_alone_cost(m[i]->a, &subs[i]);
+        most = std::max(most, subs[i]);
+    }
+    if (m.size() > 2 && most < 16) return true;
+    int64_t apart = 0;
+    for (size_t i = 0; i < m.size(); ++i) apart += cost[i] * subs[i];
+    return apart > 1024 * most * ((blocks + 255) / 256);
+}
+
 // the launch parameters of the next n transitions of a fused request
 FusedRun tick_run(const Request* q, int64_t n) {
     FusedRun r;
@@ -262,8 +289,14 @@ void worker_loop(hmc_server* srv) {
                 others.push_back(q);
             }
         }
-        for (auto& kv : lr16_classes)   // a class of one runs as an ordinary plain request
-            if (kv.second.size() == 1) others.push_back(kv.second[0]);
+        for (auto it = lr16_classes.begin(); it != lr16_classes.end();) {
+            if (lr16_share(it->second)) {
+                ++it;
+            } else {                    // ordinary plain requests
+                others.insert(others.end(), it->second.begin(), it->second.end());
+                it = lr16_classes.erase(it);
+            }
+        }
         bool ok = true;
         int njob = 0;
         for (auto& kv : classes) {
@@ -300,7 +333,6 @@ void worker_loop(hmc_server* srv) {
         int si = 1;
         int nlr = 0;
         for (auto& kv : lr16_classes) {
-            if (kv.second.size() < 2) continue;
             for (size_t b0 = 0; b0 < kv.second.size() && ok; b0 += kMaxJobs) {
                 const size_t b1 = std::min(kv.second.size(), b0 + kMaxJobs);
                 hipStream_t s = srv->streams[si++ % kStreams];

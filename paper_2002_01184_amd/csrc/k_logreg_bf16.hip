@@ -1249,6 +1249,21 @@ static hipError_t lb_few_launch(const PlainArgs& a, const float* x, const float*
     return hipGetLastError();
 }
 
+// Chain tiles per workgroup of the few-chain kernel, 0: the many-chain kernel.  As few
+// chains per workgroup as lets its workgroups (one per CU) run in one round, or up to
+// D = 256 in one and a half: a round of 64 chains takes half the time of the 256-chain
+// kernel's, which any number of chains up to a full round takes (beyond D = 256, two
+// thirds of the 128-chain one's).  Per gradient and its partial sum: 20011 x 150, 200
+// chains 140 -> 32 us; 30000 x 250, 1000 chains 255 -> 76, 2000 chains 260 -> 115, 3000
+// chains 265 -> 214; 30000 x 512, 2048 chains 274 -> 195.  Past the line: 50000 x 256,
+// 4000 chains 350 in two rounds against 304; 30000 x 512, 3000 chains 342 against 293.
+static int lb_few_cs(int ks, int64_t C, int nsplit) {
+    auto blocks = [&](int cs) { return (C + 16 * cs - 1) / (16 * cs) * nsplit; };
+    if (blocks(1) <= 256) return 1;
+    if (blocks(2) <= 256) return 2;
+    return blocks(4) <= (ks <= 8 ? 384 : 256) ? 4 : 0;
+}
+
 template <int KS>
 static hipError_t lb_grad_k(const PlainArgs& a, const float* x, const float* p, int drift, hipStream_t s) {
     using P = LbGrad<KS>;
@@ -1256,18 +1271,11 @@ static hipError_t lb_grad_k(const PlainArgs& a, const float* x, const float* p, 
     const int nsplit = lb_grad_nsplit_t(a);
     const int64_t NP = (a.tg.N + LB_RS - 1) / LB_RS * LB_RS;
     const int64_t rows = rows_for(NP, nsplit);
-    // The few-chain kernel, with as few chains per workgroup as lets its workgroups
-    // (one per CU) run in one round, or up to D = 256 in one and a half: a round of
-    // 64 chains takes half the time of the 256-chain kernel's, which any number of
-    // chains up to a full round takes (beyond D = 256, two thirds of the 128-chain
-    // one's).  Per gradient and its partial sum: 20011 x 150, 200 chains 140 -> 32 us;
-    // 30000 x 250, 1000 chains 255 -> 76, 2000 chains 260 -> 115, 3000 chains 265 ->
-    // 214; 30000 x 512, 2048 chains 274 -> 195.  Past the line: 50000 x 256, 4000
-    // chains 350 in two rounds against 304; 30000 x 512, 3000 chains 342 against 293.
-    auto blocks = [&](int cs) { return (a.C + 16 * cs - 1) / (16 * cs) * nsplit; };
-    if (blocks(1) <= 256) return lb_few_launch<KS, 1>(a, x, p, drift, nsplit, rows, s);
-    if (blocks(2) <= 256) return lb_few_launch<KS, 2>(a, x, p, drift, nsplit, rows, s);
-    if (blocks(4) <= (KS <= 8 ? 384 : 256)) return lb_few_launch<KS, 4>(a, x, p, drift, nsplit, rows, s);
+    switch (lb_few_cs(KS, a.C, nsplit)) {
+    case 1: return lb_few_launch<KS, 1>(a, x, p, drift, nsplit, rows, s);
+    case 2: return lb_few_launch<KS, 2>(a, x, p, drift, nsplit, rows, s);
+    case 4: return lb_few_launch<KS, 4>(a, x, p, drift, nsplit, rows, s);
+    }
     const size_t lds = (size_t)P::LDS;
     if (lds > 65536)
         (void)hipFuncSetAttribute((const void*)k_lr16_grad_pipe<KS>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1313,6 +1321,15 @@ int lr16_batch_class(const PlainArgs& a) {
     if (a.tg.kind != HMC_TGT_LOGREG || !a.bf16_grad || a.f64) return -1;
     const int ks = lb_ks(a.tg.D);
     return ks > 0 ? ks : -1;
+}
+
+int64_t lr16_alone_cost(const PlainArgs& a, int64_t* subs) {
+    const int ns = lb_grad_nsplit_t(a);
+    *subs = rows_for((a.tg.N + LB_RS - 1) / LB_RS * LB_RS, ns) / LB_RS;
+    const int cs = lb_few_cs(lb_ks(a.tg.D), a.C, ns);
+    if (cs == 0) return 1024;
+    const int64_t blocks = (a.C + 16 * cs - 1) / (16 * cs) * ns;
+    return cs == 1 ? blocks : (cs == 2 ? 3 * blocks / 2 : 5 * blocks / 2);
 }
 
 void lr16_job_shape(const PlainArgs& a, Lr16Job* j) {
