@@ -297,6 +297,18 @@ void worker_loop(hmc_server* srv) {
                 it = lr16_classes.erase(it);
             }
         }
+        // an element-wise request alone in its class runs as sample_chain would run it (the
+        // few-chain kernel is not in the ragged launch): us a transition, N(0, 1) FP64, 100
+        // chains 3.5 -> 2.4, D = 333, 1000 chains 4.4 -> 3.5; two share (D = 100, 200 chains
+        // 3.6, apart 3.7; four 3.9, 8.0)
+        for (auto it = classes.begin(); it != classes.end();) {
+            if (it->second.size() > 1) {
+                ++it;
+            } else {
+                others.push_back(it->second[0]);
+                it = classes.erase(it);
+            }
+        }
         bool ok = true;
         int njob = 0;
         for (auto& kv : classes) {

@@ -51,3 +51,27 @@ def test_few_run_side_by_side(n, N, D, C):
 def test_many_share(n, N, D, C):
     st = _served(_requests(n, N, D, C, 200))
     assert st["batched_plain_transitions"] >= 1
+
+
+# alone in its class a request takes the kernels of sample_chain, a tick at a time, down to
+# a last tick of one transition; beside another of its class a ragged launch
+@pytest.mark.parametrize("kind,D,C,dtype", [("std", 1, 100, "f64"), ("std", 3, 700, "f32"), ("diag", 37, 200, "f32"),
+                                            ("diag", 333, 300, "f32")])
+@pytest.mark.parametrize("n", [1, 2])
+def test_element_wise_requests(kind, D, C, dtype, n):
+    if kind == "std":
+        reqs = [W.std_normal_1d(num_chains=C, dim=D, state_dtype=dtype, L=4, step_size=0.4, burnin=20, results=11,
+                                seed=70 + i) for i in range(n)]
+    else:
+        reqs = [W.gauss_diag(dim=D, num_chains=C, L=4, step_size=0.05, burnin=20, results=11, seed=70 + i)
+                for i in range(n)]
+    srv = hmc.Server(1 << 30, transitions_per_tick=5)
+    preps = [srv.prepare(w) for w in reqs]
+    outs = [srv.wait(i)[0] for i in [srv.submit_prepared(p) for p in preps]]
+    srv.close()
+    for w, o in zip(reqs, outs):
+        s = hmc.sampler_for(w)
+        ref = s.sample_chain(w.num_results, w.num_burnin, adapt=w.adapt)
+        for k in ("samples", "is_accepted", "step_size", "target_log_prob"):
+            assert torch.equal(o[k], ref[k]), (w.name, k)
+        s.close()
