@@ -879,14 +879,19 @@ bool fused_remc_inline(const PlainArgs& a, int64_t K) {
     }
 
 // The few-chain kernel: the lanes of all chains fill at most one wavefront per
-// SIMD (1024; beyond, two of fused_elem_body's wavefronts hide each other's
-// waits), and the owners' state fits the registers of 8 waves per CU.
+// SIMD (65536 lanes: 256 owner threads of a workgroup's 512 on 256 CUs), and the
+// owners' state fits the registers of 8 waves per CU.  With a lane per chain, whose
+// transitions are short beside their draws, only up to three quarters of that.  40
+// transitions at L = 3 (10), without and with: N(0, I) D = 4 FP64, 49152 chains 68.8,
+// 69.3 us, 65536 chains 70.6, 77.2 (81.5, 83.1); FP32 48.0, 45.0 and 48.7, 52.7 (59.1,
+// 52.3); D = 16 FP64, 16384 chains of four lanes 72.3, 66.9; D = 250 FP64, 1024
+// chains of 64 lanes 70.3, 68.0.
 template <typename T, int G, int NB>
 static bool launch_elem_few(const PlainArgs& a, const FusedRun& r, hipStream_t s) {
     if constexpr (NB * sizeof(T) > 16) {
         return false;
     } else {
-        if (a.C * G > 65536 || r.n_transitions < 2) return false;
+        if (a.C * G > (G == 1 ? 49152 : 65536) || r.n_transitions < 2) return false;
         const int64_t unit = r.remc_K > 1 ? r.remc_K : 1;              // a pair's chains share a wavefront
         int64_t chains = (a.C + 255) / 256;
         chains = (chains + unit - 1) / unit * unit;
