@@ -75,8 +75,15 @@ __device__ __forceinline__ void after_decision(const FusedRun& r, int64_t C, int
 // Transformed kernel (x = shift + scale z, EX): the chain runs in z = x / scale,
 // whose precision is prec scale^2; states are converted at load and store.
 // ND: dims of a block held (4, or the dims themselves where they are fewer).
+// WIDE (FP64 beyond 1024 dims): x, g, the precisions, the trajectory and its gradient
+// would take 640 of 512 registers.  The new gradient is formed again where it is used
+// after the trajectory (one product an element, the same bits), the code of a leapfrog
+// step stands once, and the state is loaded a block at a time: N(0, I) D = 2048, 3000
+// chains, 20 transitions 752 -> 616 us, one 108 -> 95; D = 1358 675 -> 570, 92 -> 84.
 template <typename T, int G, int NB, bool EX, int ND = 4>
 struct ElemChain {
+    static constexpr bool WIDE = NB * sizeof(T) > 32;
+    struct __attribute__((packed, aligned(sizeof(T)))) T4 { T v[ND]; };   // rows are at least element-aligned
     T x[NB][ND], g[NB][ND], pr[NB][ND];
     bool ok[NB][ND];
     ChainCtl s;
@@ -103,15 +110,38 @@ struct ElemChain {
         const T* X = (const T*)a.ws.x;
         const T* Gr = (const T*)a.ws.g;
         const T* prec = (const T*)a.tg.prec;
+        if constexpr (WIDE) {
+#pragma unroll
+            for (int k = 0; k < NB; ++k)
+#pragma unroll
+                for (int j = 0; j < ND; ++j) ok[k][j] = active && 4 * (lane + (int64_t)G * k) + j < D;
+            // whole blocks in a loop of their own: one loop for both kinds loses half the gain
+#pragma unroll
+            for (int k = 0; k < NB; ++k)
+                if (ok[k][ND - 1]) {
+                    const int64_t d = 4 * (lane + (int64_t)G * k);
+                    const T4 xv = *(const T4*)(X + cc * D + d), gv = *(const T4*)(Gr + cc * D + d);
+                    T4 pv;
+                    if (diag) pv = *(const T4*)(prec + d);
+#pragma unroll
+                    for (int j = 0; j < ND; ++j) {
+                        x[k][j] = xv.v[j];
+                        g[k][j] = gv.v[j];
+                        pr[k][j] = diag ? pv.v[j] : (T)1;
+                    }
+                }
+        }
 #pragma unroll
         for (int k = 0; k < NB; ++k)
 #pragma unroll
             for (int j = 0; j < ND; ++j) {
                 const int64_t d = 4 * (lane + (int64_t)G * k) + j;
-                ok[k][j] = active && d < D;
-                x[k][j] = ok[k][j] ? X[cc * D + d] : (T)0;
-                g[k][j] = ok[k][j] ? Gr[cc * D + d] : (T)0;
-                pr[k][j] = ok[k][j] ? (diag ? prec[d] : (T)1) : (T)0;
+                if (!WIDE) ok[k][j] = active && d < D;
+                if (!(WIDE && ok[k][ND - 1])) {
+                    x[k][j] = ok[k][j] ? X[cc * D + d] : (T)0;
+                    g[k][j] = ok[k][j] ? Gr[cc * D + d] : (T)0;
+                    pr[k][j] = ok[k][j] ? (diag ? prec[d] : (T)1) : (T)0;
+                }
                 if (sc && ok[k][j]) {
                     const double sd = sc[d];
                     pr[k][j] = (T)((double)pr[k][j] * sd * sd);
@@ -139,7 +169,8 @@ struct ElemChain {
         const T eps = (T)s.eps;                   // drift
         const T half = (T)(0.5 * s.eps * bt);     // kicks: beta eps (replica exchange; beta = 1 otherwise)
         const T keps = (T)(s.eps * bt);
-        T xn[NB][ND], pn[NB][ND], gn[NB][ND];
+        T xn[NB][ND], pn[NB][ND], gk[WIDE ? 1 : NB][ND];
+        auto gn = [&](int k, int j) { return WIDE ? -pr[k][j] * xn[k][j] : gk[WIDE ? 0 : k][j]; };
         // dk and lp are summed without their factor 1/2 (exact in binary, applied below)
         double dk = 0.0;
 #pragma unroll
@@ -160,14 +191,15 @@ struct ElemChain {
 #pragma unroll
                 for (int j = 0; j < ND; ++j) {
                     xn[k][j] = fma(eps, pn[k][j], xn[k][j]);
-                    gn[k][j] = -pr[k][j] * xn[k][j];
-                    pn[k][j] = fma(ke, gn[k][j], pn[k][j]);
+                    const T gv = -pr[k][j] * xn[k][j];
+                    if (!WIDE) gk[WIDE ? 0 : k][j] = gv;
+                    pn[k][j] = fma(ke, gv, pn[k][j]);
                 }
         };
         // The last step apart: in FP64 the choice of the factor in the chain of
         // dependent operations is not free (D = 1 run 158 -> 154 us, D = 37 135 ->
         // 128); in FP32 the shorter code is (D = 1000, 1000 chains 907 against 934).
-        if constexpr (sizeof(T) == 8) {
+        if constexpr (sizeof(T) == 8 && !WIDE) {
             for (int l = 1; l < a.L; ++l) leap(keps);
             leap(half);
         } else {
@@ -179,7 +211,7 @@ struct ElemChain {
 #pragma unroll
             for (int j = 0; j < ND; ++j) {
                 dk = fma((double)pn[k][j], (double)pn[k][j], dk);
-                lp = fma((double)xn[k][j], (double)gn[k][j], lp);
+                lp = fma((double)xn[k][j], (double)gn(k, j), lp);
             }
         dk = 0.5 * group_sum<G>(dk);
         lp = 0.5 * group_sum<G>(lp);
@@ -192,13 +224,11 @@ struct ElemChain {
 #pragma unroll
                 for (int j = 0; j < ND; ++j) {
                     x[k][j] = xn[k][j];
-                    g[k][j] = gn[k][j];
+                    g[k][j] = gn(k, j);
                 }
             s.logp = lp;
         }
-        // four dims of a row at p + d, as one store where the block is whole (rows are
-        // at least element-aligned)
-        struct __attribute__((packed, aligned(sizeof(T)))) T4 { T v[ND]; };
+        // four dims of a row at p + d, as one store where the block is whole
         auto store4 = [&](T* p, int k, const T (&v)[ND]) {
             if (ok[k][ND - 1]) {
                 T4 o;
