@@ -68,5 +68,16 @@ def build(verbose: bool = False, jobs: int = 8, sanitize: bool = False, out: str
     return out
 
 
+# The check of the device functions that the GPU tests load (tests/device_check.hip).
+DEVICE_CHECK = os.path.join(ROOT, "tests", "libdevice_check.so")
+
+
+def build_device_check() -> str:
+    tmp = DEVICE_CHECK + ".tmp"
+    subprocess.check_call([HIPCC, *FLAGS, "-shared", os.path.join(ROOT, "tests", "device_check.hip"), "-o", tmp])
+    os.replace(tmp, DEVICE_CHECK)
+    return DEVICE_CHECK
+
+
 if __name__ == "__main__":
     print(build(verbose="-v" in sys.argv))
