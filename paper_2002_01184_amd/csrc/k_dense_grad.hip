@@ -16,9 +16,10 @@
 // the operand layout and MFMA sequence of the fused dense kernel and of
 // k_dense_step, so all forms give bitwise the same gradient.  P and x go
 // through LDS 16 k-steps at a time (four 16-column pieces of every row, loaded
-// 16 bytes a lane into registers two chunks ahead; two workgroups fit a CU),
-// each lane reading the operands of 4 k-steps with one ds_read_b128 (row stride
-// 84 floats: 8 consecutive rows hit distinct bank quads).
+// 16 bytes a lane into registers two chunks ahead; a CU's LDS holds three
+// workgroups of one chain tile or two of two), each lane reading the operands of
+// 4 k-steps with one ds_read_b128 (row stride 84 floats: 8 consecutive rows hit
+// distinct bank quads).
 //
 // The kernel it replaces gave each workgroup 16 chains and all of P, read from
 // global memory 4 bytes a lane at a stride of a row: 48.9 us per step at D = 300,

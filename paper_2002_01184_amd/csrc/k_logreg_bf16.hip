@@ -208,7 +208,7 @@ __device__ __forceinline__ void lb_load_theta(const PlainArgs& a, const float* _
 // beside its X^T tile, or (beyond D = 256) read from global memory by each lane.
 //
 // What bounds it: power and the matrix cores.  At D = 256, N = 100000, 8192 chains
-// the MFMAs fill 54% -> 61% of the clocks (3800 -> 3340 a sub-tile), and the clock
+// the MFMAs fill 54% -> 60% of the clocks (3800 -> 3340 a sub-tile), and the clock
 // falls with it, 2.20 -> 2.12 GHz: 704 -> 656 us a gradient (1.28 PFLOP/s).  With
 // half the CUs (50000 rows, 4000 chains) 356 -> 304 us, D = 128 214 -> 190, D = 100
 // (4096 chains) 194 -> 157, D = 500 399 -> 385 (gradient and its finish).
@@ -486,10 +486,9 @@ __device__ __forceinline__ void lr16_grad_body(const PlainArgs& a, const float* 
     };
     if (nsub > 0) {
 #pragma unroll
-        for (int u = 0; u < 2 * SUBS; ++u) {
+        for (int u = 0; u <= SUBS; ++u) {
 #pragma unroll
-            for (int k = 0; k < J; ++k)
-                if (u <= SUBS) copy_k(u, k, xring + (u % NBX) * XB, tring + (u % NBT) * TBY);
+            for (int k = 0; k < J; ++k) copy_k(u, k, xring + (u % NBX) * XB, tring + (u % NBT) * TBY);
             if (u == SUBS - 1) {
                 wait_vmcnt<0>();       // the only copies outstanding are the first stage's
                 lds_barrier();

@@ -7,8 +7,9 @@
 // 8 + 8 + 8 bits), and a BF16 x BF16 product is exact in FP32, so with FP32
 // accumulation
 //     X in BF16: 3 products   x (t_h + t_m + t_l)        -- every product formed
-//     X in FP32: 8 products   of the 3 x 3; the one left out is below 2^-31
-//                             of the leading one
+//     X in FP32: 8 products   of the 3 x 3; the one left out is below 2^-30
+//                             of the leading one (a third term cut off is below
+//                             2^-15 of its number)
 // give the FP32 result with fewer roundings than v_mfma_f32_16x16x4f32, which
 // rounds its accumulator after every 4 terms where v_mfma_f32_16x16x32_bf16
 // rounds after 32 (six products, leaving out those below 2^-23, had twice the
@@ -16,12 +17,12 @@
 // SIMD and the eight FP32 MFMAs of the same block 256, so the split costs 48
 // (128 for FP32 X) against 256.
 //
-// Against the FP32-MFMA kernel before it, per leapfrog step with its partial
-// sum, and the gradient's error against 64 bits (2-norm, one step, before and
-// after): 100000 x 256, BF16 X, 2048 chains 2618 -> 523 us, 9.8e-7 -> 6.1e-7;
-// 20000 x 400, BF16 X, 2000 chains 1401 -> 370 us, 1.5e-6 -> 6.6e-7; 5000 x 300,
-// FP32 X, 700 chains 325 -> 84 us, 1.4e-6 -> 4.9e-7; 10000 x 25, FP32 X, 1024
-// chains 86 -> 28.5 us, 3.1e-7 -> 2.4e-7.  At 100000 x 256 the MFMAs take 0.28
+// Against the FP32-MFMA kernel before it, a twentieth of a transition of 20 leapfrogs
+// with its log-probability, and the gradient's error against 64 bits (2-norm, one
+// step; before and after): 100000 x 256, BF16 X, 2048 chains 2613 -> 618 us, 9.8e-7 -> 5.8e-7;
+// 20000 x 400, BF16 X, 2000 chains 1400 -> 317 us, 1.5e-6 -> 4.6e-7; 5000 x 300,
+// FP32 X, 700 chains 325 -> 84 us, 1.4e-6 -> 4.0e-7; 10000 x 25, FP32 X, 1024
+// chains 84 -> 28.9 us, 3.1e-7 -> 1.4e-7.  At 100000 x 256 the MFMAs take 0.28
 // ms; the rest is the residuals' vector work (14 instructions and two
 // transcendentals each) and the waits of two waves per SIMD, which theta's
 // three terms and G (160 registers) allow.  At D <= 64 the residuals bound it.
@@ -126,7 +127,8 @@ struct LsShape {
 // alignment the row has; the last slot of a row may read into the next row, and
 // those columns are masked when the unit is stored.  Only the last unit of X
 // itself is read element by element.  Offsets do not change from stage to stage.
-struct __attribute__((packed, aligned(2))) raw16 { uint4 v; };
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+struct __attribute__((packed, aligned(2))) raw16 { u32x4 v; };
 
 template <int XT, int KS>
 struct LsStage {
@@ -135,7 +137,7 @@ struct LsStage {
     static constexpr int WV = XT == 1 ? 4 : 8;               // words per unit
     uint32_t raw[NV * WV];
     uint32_t goff[NV];                                       // element offset from the stage's first element
-    uint32_t loff[NV];                                       // LDS byte offset, row << 20 (row < LS_RS <= 128)
+    uint32_t loff[NV];                                       // LDS byte offset, row << 20 (up to 255: past the stage for narrow X)
     int nv_last;                                             // valid columns of a row's last slot
     int nel_row;                                             // D
 
@@ -186,10 +188,10 @@ struct LsStage {
         }
     }
     __device__ __forceinline__ void load_unit(int k, const char* p) {
-        const uint4 v = ((const raw16*)p)->v;
+        const u32x4 v = ((const raw16*)p)->v;
         raw[WV * k] = v.x; raw[WV * k + 1] = v.y; raw[WV * k + 2] = v.z; raw[WV * k + 3] = v.w;
         if constexpr (XT == 3) {
-            const uint4 u = ((const raw16*)(p + 16))->v;
+            const u32x4 u = ((const raw16*)(p + 16))->v;
             raw[WV * k + 4] = u.x; raw[WV * k + 5] = u.y; raw[WV * k + 6] = u.z; raw[WV * k + 7] = u.w;
         }
     }
@@ -560,13 +562,13 @@ static hipError_t ls_ks(const PlainArgs& a, const float* x, const float* p, int 
     return hipErrorInvalidValue;
 }
 
-// Row splits of a launch, within the partials the workspace holds: two
-// workgroups of 64 chains per CU (one beyond D = 256) as long as a split keeps
-// two sub-tiles, then
-// up to the waves that the registers let a SIMD hold (4 at D <= 64) while a
-// split keeps 256 rows, below which the partials that k_logreg_finish adds cost
-// more than the waves give (10000 x 25, 1024 chains: 28.6 us per step at 32
-// splits, 30.8 at 64; 6931 x 12, 3691 chains: 47.7 us at 16 splits, 52.7 at 8).
+// Row splits of a launch, at most the 64 (a quarter of the CUs at 64 chains or
+// fewer) whose partials the workspace holds: two workgroups of 64 chains per CU (one
+// beyond D = 256) as long as a split keeps two sub-tiles, then up to the waves that
+// the registers let a SIMD hold (4 at D <= 64) while a split keeps 256 rows, below
+// which the partials that k_logreg_finish adds cost more than the waves give
+// (10000 x 25, 1024 chains: 28.6 us per step at 32 splits, 30.8 at 64; 6931 x 12,
+// 3691 chains: 47.7 us at 16 splits, 52.7 at 8).
 int lr32_nsplit(const PlainArgs& a) {
     const int64_t cap = logreg_nsplit_cap(a.tg.N, a.C);
     if (a.tune.lr_nsplit > 0) return (int)(a.tune.lr_nsplit < cap ? a.tune.lr_nsplit : cap);

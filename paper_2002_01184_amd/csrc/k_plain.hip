@@ -783,6 +783,7 @@ __global__ __launch_bounds__(64 * DS_NW) void k_dense_step(PlainArgs a) {
 // and only start from this one: it keeps the arithmetic, so that a seed's chains
 // stay the same bit for bit, where the split kernel (k_logreg_f32.hip) rounds
 // differently.  The plain form starts, steps and resumes there.
+//
 // A workgroup (4 waves) owns 64 chains and one split of the rows; wave w runs
 // both contractions for chains c0 + 16 w + i16 over the split's rows, 16 rows
 // at a time:
