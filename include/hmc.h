@@ -172,7 +172,9 @@ hmc_status hmc_get_state(hmc_ctx* ctx, void* state, double* step_size, uint64_t*
 /* Resume: replaces the state (device [C, D]) and, if step_size (device [C],
  * FP64) is not NULL, the step sizes; recomputes the cached logp and gradient;
  * sets the transition counter to t.  Runs resumed this way reproduce an
- * uninterrupted run bit for bit. */
+ * uninterrupted run bit for bit, except logistic regression in the fused form,
+ * whose kernel carries a gradient of its own summation order: there the resumed
+ * run starts from the same state with a gradient that may differ by rounding. */
 hmc_status hmc_set_state(hmc_ctx* ctx, const void* state, const double* step_size, uint64_t t);
 
 /* Frees the context (synchronizes its stream first).  NULL is a no-op. */

@@ -5,9 +5,10 @@
 //   1. admits queued requests whose memory fits the free part of the device
 //      pool (first fit, arrival order with backfill), runs their bootstrap;
 //   2. advances every active request by up to transitions_per_tick
-//      transitions: elementwise requests of one shape class in a single ragged
-//      launch (a device job table maps blocks to requests), every other request
-//      on one of a few HIP streams so their kernels overlap on the device;
+//      transitions: elementwise requests that share a shape class in a single
+//      ragged launch (a device job table maps blocks to requests), BF16 logistic
+//      ones of a class in shared launches where lr16_share says so, every other
+//      request on one of a few HIP streams so their kernels overlap on the device;
 //   3. retires requests that reached burn-in + results transitions and frees
 //      their memory (or keeps server-owned samples until hmc_server_take).
 // Chain state, gradients, log-probabilities, step sizes and dual-averaging
